@@ -57,6 +57,9 @@ hipError_t launch_rope_tables(const int32_t* positions, int T, int d,
 hipError_t launch_map(const MapArgs& a, int dtype, int d, int style,
                       hipStream_t stream);
 
+// The bf16 side of launch_map (kvx_map_tile.hip).
+hipError_t launch_map_tile(const MapArgs& a, int d, int style, hipStream_t stream);
+
 // W-stationary kernel (bf16, d = 128, k <= 4); needs a.cs16, a.cs16_tgt and
 // a.range_len.
 bool map_w_supported(int dtype, int d, int k);

@@ -1,0 +1,67 @@
+"""Parity of the bf16 tile kernels with the fp64 oracle: head dimension 64 with
+the maps resident (k <= 8) and streamed (k > 8), head dimension 128 with more
+than four source layers; ragged tiles, both RoPE layouts, unequal RoPEs, dense
+and slot-addressed targets."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_03893_amd import synth
+from _parity import TOL, assert_parity, np32, oracle_rows, run_gpu
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+Q = synth.CONFIGS["qwen3_14b_32b"].replace(L_s=12, L_t=3, H=2)
+I1 = synth.rope_dict(1e6, style=1)
+
+CASES = {
+    "d64_k1_T1": Q.replace(d=64, k=1, T=1),
+    "d64_k4_T257_rebase": Q.replace(d=64, k=4, T=257, rope_src=synth.rope_dict(1e4)),
+    "d64_k8_H3_T1030_interleaved": Q.replace(d=64, k=8, H=3, T=1030, rope_src=I1, rope_tgt=I1),
+    # long ranges: several tiles a workgroup and a short last range
+    "d64_k3_T2600_long_ranges": Q.replace(d=64, k=3, H=8, L_t=40, T=2600, bias="none"),
+    "d64_k9_T300_streamed": Q.replace(d=64, k=9, T=300),
+    "d128_k5_T255": Q.replace(k=5, T=255, bias="none"),
+    "d128_k8_H3_T513_rebase": Q.replace(k=8, H=3, T=513, rope_src=synth.rope_dict(1e4)),
+    "d128_k6_T16_interleaved": Q.replace(k=6, T=16, rope_src=I1, rope_tgt=I1),
+    "d128_k11_T700": Q.replace(k=11, T=700),
+    # more items than workgroups: the pipeline runs across items
+    "d128_k5_L24_H8_T520": Q.replace(k=5, H=8, L_t=24, T=520),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_tile_parity(gpu_kvx, name):
+    cfg = CASES[name]
+    inp = synth.make_inputs(cfg, DEV)
+    out = run_gpu(gpu_kvx, inp)
+    assert_parity(np32(out), oracle_rows(inp), TOL["bf16"], name)
+
+    # the same rows through slots in reverse order, every seventh left out
+    T = cfg.T
+    slots = torch.arange(T - 1, -1, -1, dtype=torch.int32, device=DEV) + 5
+    slots[::7] = -1
+    pool = torch.full((cfg.L_t, 2, cfg.H, T + 9, cfg.d), 7.0, dtype=torch.bfloat16, device=DEV)
+    gpu_kvx.map_cache_slots(inp["src"], inp["idx"], inp["W_K"], inp["W_V"], inp["b_K"], inp["b_V"],
+                            inp["rope_src"], inp["rope_tgt"], inp["positions"], slots, pool)
+    torch.cuda.synchronize()
+    want = torch.full_like(pool, 7.0)
+    keep = (slots >= 0).nonzero()[:, 0]
+    want[:, :, :, slots[keep].long()] = out[:, :, :, keep]
+    assert torch.equal(pool, want), name
+
+
+@pytest.mark.parametrize("d,k", [(64, 2), (128, 5)])
+def test_tile_kernel_leaves_non_finite_rows_alone(gpu_kvx, d, k):
+    """A token whose source row holds infinities or NaN spoils its own output row only."""
+    cfg = Q.replace(d=d, k=k, T=130)
+    inp = synth.make_inputs(cfg, DEV)
+    clean = run_gpu(gpu_kvx, inp)
+    inp["src"][:, :, :, 129] = float("inf")
+    inp["src"][:, :, :, 17, 3] = float("nan")
+    out = run_gpu(gpu_kvx, inp)
+    rest = torch.from_numpy(np.setdiff1d(np.arange(cfg.T), [17, 129])).to(DEV)
+    assert torch.equal(out[:, :, :, rest], clean[:, :, :, rest])
+    assert not bool(torch.isfinite(out[:, :, :, 17].float()).any())
+    assert not bool(torch.isfinite(out[:, :, :, 129].float()).all())
