@@ -151,14 +151,29 @@ Tables tables(const kvx_dims& m, void* ws, bool same) {
   return t;
 }
 
-// Tokens per workgroup of the W-stationary kernel: long enough to amortise
-// staging the map, a multiple of the 256-token tile.  The environment
-// variable KVX_TOKENS_PER_WG overrides it (tuning only).
-int tokens_per_wg() {
-  const char* e = std::getenv("KVX_TOKENS_PER_WG");
-  int r = (e != nullptr && std::atoi(e) > 0) ? std::atoi(e) : 4096;
-  if (r > (1 << 30)) r = 1 << 30;
-  return ((r + 255) / 256) * 256;
+// Tokens per workgroup of the W-stationary kernel, in 256-token tiles, at most
+// 16: the length with the shortest last round when one workgroup fits a CU
+// (256 of them) and staging a map costs about one tile's time.  A fixed 4096
+// tokens left 240 CUs idle for one layer of 4096 tokens (185 us; 256 tokens a
+// workgroup: 18 us) and a last round half empty for a one-head cache of 80
+// layers and 16384 tokens.  The environment variable KVX_TOKENS_PER_WG
+// overrides it (tuning only).
+int tokens_per_wg(int64_t tasks, int64_t T) {
+  if (const char* e = std::getenv("KVX_TOKENS_PER_WG")) {
+    const int r = std::atoi(e);
+    if (r > 0) return ((r > (1 << 30) ? 1 << 30 : r) + 255) / 256 * 256;
+  }
+  const int64_t tiles = (T + 255) / 256;
+  int64_t best = 0, best_cost = 0;
+  for (int64_t n = 1; n <= 16; ++n) {
+    const int64_t items = (tiles + n - 1) / n * tasks;
+    const int64_t cost = (items + 255) / 256 * (n + 1);
+    if (best == 0 || cost <= best_cost) {
+      best = n;
+      best_cost = cost;
+    }
+  }
+  return (int)best * 256;
 }
 
 struct Call {
@@ -316,7 +331,7 @@ kvx_status run(const Call& c) {
   a.cs_tgt = tb.cs_tgt;
   a.cs16 = tb.cs16;
   a.cs16_tgt = tb.cs16_tgt;
-  a.range_len = tokens_per_wg();
+  a.range_len = tokens_per_wg((int64_t)c.nl * m.H * 2, m.T);
   {
     const char* e = std::getenv("KVX_WAVE_TOKENS");  // tuning only
     a.wave_tokens = (e != nullptr && std::atoi(e) == 64) ? 64 : 32;
