@@ -154,9 +154,8 @@ Tables tables(const kvx_dims& m, void* ws, bool same) {
 // Tokens per workgroup of the W-stationary kernel, in 256-token tiles, at most
 // 16: the length with the shortest last round when one workgroup fits a CU
 // (256 of them) and staging a map costs about one tile's time.  A fixed 4096
-// tokens left 240 CUs idle for one layer of 4096 tokens (185 us; 256 tokens a
-// workgroup: 18 us) and a last round half empty for a one-head cache of 80
-// layers and 16384 tokens.  The environment variable KVX_TOKENS_PER_WG
+// tokens left 240 CUs idle for one layer of 4096 tokens and 8 heads (a call of
+// 190 us; 256 tokens a workgroup: 26.5 us).  The environment variable KVX_TOKENS_PER_WG
 // overrides it (tuning only).
 int tokens_per_wg(int64_t tasks, int64_t T) {
   if (const char* e = std::getenv("KVX_TOKENS_PER_WG")) {
@@ -291,10 +290,12 @@ Kernel choose_kernel(int dt, const kvx_dims& m, int nl, int64_t tgt_rows, bool s
     if (std::strcmp(e, "ks2") == 0 && ks2_ok) return Kernel::Ks2;
   }
   // The sweep kernels keep every compute unit busy for any layer count (their
-  // layer groups fill the 32 CUs of an XCD), but need the heads to spread
-  // evenly over the eight XCDs, and enough layers per group to amortise
-  // each unit's start (loading the maps, filling the pipeline).
-  if (m.H % 8 == 0 && nl >= 16) {
+  // layer groups fill the 32 CUs of an XCD), but need the units of a group to
+  // spread evenly over the eight XCDs (by heads, or by heads and token
+  // segments), and enough layers per group to amortise each unit's start
+  // (loading the maps, filling the pipeline).
+  const int segs = kvx::plan_sweep(nl, m.H, m.T).segs;
+  if (m.H * segs % 8 == 0 && nl >= 16) {
     if (ks2_ok) return Kernel::Ks2;
     if (ks_ok) return Kernel::Ks;
     return Kernel::Sweep;
@@ -349,15 +350,20 @@ kvx_status run(const Call& c) {
       a.idx[l * m.k + i] = (uint8_t)c.idx[(int64_t)(c.l0 + l) * m.k + i];
   hipError_t e = hipSuccess;
   if (wpath) {
+    // The kernels read W as given and leave the packed images for later calls;
+    // the layer-sweep kernel reads the images.
     a.wpack = static_cast<char*>(c.ws) + tables_bytes(m);
-    if (!(c.flags & KVX_FLAG_WEIGHTS_PACKED)) {
-      e = kvx::launch_pack_w(a, const_cast<void*>(a.wpack), c.stream);
+    a.raw_w = (c.flags & KVX_FLAG_WEIGHTS_PACKED) == 0;
+    if (a.raw_w && kern == Kernel::Sweep) {
+      e = kvx::launch_pack_w(a, a.wpack, c.stream);
       if (e != hipSuccess) return fail(KVX_ERR_HIP, "weight packing launch: %s", hipGetErrorString(e));
     }
     if (kern == Kernel::Ks)
-      e = kvx::launch_map_ks(a, kvx::plan_sweep(c.nl, m.H, m.T), c.rs->style, c.stream);
+      e = (a.raw_w ? kvx::launch_map_ks_raw : kvx::launch_map_ks)(
+          a, kvx::plan_sweep(c.nl, m.H, m.T), c.rs->style, c.stream);
     else if (kern == Kernel::Ks2)
-      e = kvx::launch_map_ks2(a, kvx::plan_sweep(c.nl, m.H, m.T), c.rs->style, c.stream);
+      e = (a.raw_w ? kvx::launch_map_ks2_raw : kvx::launch_map_ks2)(
+          a, kvx::plan_sweep(c.nl, m.H, m.T), c.rs->style, c.stream);
     else if (kern == Kernel::Sweep)
       e = kvx::launch_map_sweep(a, kvx::plan_sweep(c.nl, m.H, m.T), c.rs->style, c.stream);
     else

@@ -33,7 +33,7 @@ struct MapArgs {
   const float2* cs_tgt;   // [T, d/2] (cos, sin) of the target RoPE
   const void* cs16;       // [T, d/2] (cos, sin) of the source RoPE as fp16 pairs
   const void* cs16_tgt;   // [T, d/2] (cos, sin) of the target RoPE as fp16 pairs
-  const void* wpack;      // packed map images [L_t, H, 2, d, k*d] (W-stationary kernel)
+  void* wpack;            // packed map images [L_t, H, 2, d, k*d]
   void* tgt;              // [L_t, 2, H, rows, d]
   const int32_t* slots;   // [T] or nullptr (dense)
   int64_t tgt_rows;       // T (dense) or num_slots (slot-addressed)
@@ -42,6 +42,7 @@ struct MapArgs {
   int32_t nl;             // number of target layers in this launch
   int32_t range_len;      // tokens per workgroup (W-stationary kernel)
   int32_t wave_tokens;    // tokens per wave per tile, 32 or 64 (W-stationary kernel)
+  int32_t raw_w;          // read the maps from wk / wv and write wpack; 0: read wpack
   uint8_t idx[kMaxIdx];   // idx[(l - l0) * k + i]
 };
 
@@ -75,22 +76,91 @@ hipError_t launch_pack_w(const MapArgs& a, void* wp, hipStream_t stream);
 // so that every group's layer pairs times token parts fill the 32 CUs of an
 // XCD exactly; a unit of work is (group, head, K|V).
 struct SweepPlan {
-  int32_t n_units;       // n_groups * H * 2
+  int32_t n_units;       // n_groups * H * segs * 2
+  int32_t segs;          // token segments: spread few or odd heads over the XCDs
   int32_t n_groups;      // full_groups + n_rest
   int32_t full_groups;   // leading groups of 64 layers
   int32_t n_rest;        // remainder groups, at most 6
   int32_t rest_len[6];   // their sizes (descending powers of two)
 };
+// Least 16-token tiles that a unit of a segmented plan has for a CU on average
+// (a group of n layers gives a CU n / 64 of the segment).  A unit starts in
+// about 8 us, loading its maps, and takes 1.25 us a tile of two layers; the
+// W-stationary kernel takes 14-20 us for 256 tokens of one layer.  At 20 tiles
+// (40 layers, one head, 8192 tokens) 134 us against 200; at 10 (20 layers, 6
+// heads, 4096 tokens, k = 3) 227 against 187.
+constexpr int kSegTiles = 20;
 SweepPlan plan_sweep(int nl, int H, int64_t T);
+
+// Unit u -> (group, K|V, head, token segment) and the CU slot's layer pair and
+// tokens within it.  Within a group, keys cost more vector work than values
+// (two rotations), so when the units of one kind divide evenly over the eight
+// XCDs every XCD takes both kinds.
+struct SweepUnit {
+  int kv, h, g0, g_n, pair;   // layers g0 .. g0 + g_n - 1; pair 2 pair, 2 pair + 1 of them
+  bool first;                 // the slot with the pair's first tokens
+  int64_t t_begin, t_end;     // empty: nothing for this slot
+};
+__device__ __forceinline__ SweepUnit sweep_unit_of(const SweepPlan& p, int unit, int slot, int H,
+                                                   int32_t T, int tile) {
+  SweepUnit q;
+  const int n = H * p.segs;
+  const int g = unit / (2 * n);
+  const int rem = unit % (2 * n);
+  int hs;
+  if (n % 8 == 0) {
+    q.kv = (rem >> 3) & 1;
+    hs = (rem & 7) | ((rem >> 4) << 3);
+  } else {
+    q.kv = rem & 1;
+    hs = rem >> 1;
+  }
+  const int seg = p.segs == 1 ? 0 : hs / H;
+  q.h = hs - seg * H;
+  if (g < p.full_groups) {
+    q.g0 = 64 * g;
+    q.g_n = 64;
+  } else {
+    q.g0 = 64 * p.full_groups;
+    q.g_n = 0;
+    for (int r = 0; r < p.n_rest; ++r) {
+      if (r == g - p.full_groups) q.g_n = p.rest_len[r];
+      else if (r < g - p.full_groups) q.g0 += p.rest_len[r];
+    }
+  }
+  // this CU's layer pair and token part (pairs * parts = 32)
+  const int pairs = (q.g_n + 1) / 2;
+  const int parts = 32 / pairs;
+  q.pair = slot % pairs;
+  const int part = slot / pairs;
+  // 32-bit arithmetic: a 64-bit division costs a microsecond per unit
+  const uint32_t up = (uint32_t)tile - 1;   // tile: a power of two
+  const uint32_t seg_len = (((uint32_t)T + p.segs - 1) / p.segs + up) & ~up;
+  const uint64_t s0 = (uint64_t)seg * seg_len;
+  if (part >= parts || s0 >= (uint64_t)T) {
+    q.t_begin = q.t_end = 0;
+  } else {
+    const uint32_t len = (uint32_t)T - (uint32_t)s0 < seg_len ? (uint32_t)T - (uint32_t)s0 : seg_len;
+    const uint32_t part_len = ((len + parts - 1) / parts + up) & ~up;
+    const uint64_t off = (uint64_t)part * part_len;
+    q.t_begin = (int64_t)(s0 + (off < len ? off : len));
+    q.t_end = (int64_t)(s0 + (off + part_len < len ? off + part_len : len));
+  }
+  q.first = seg == 0 && part == 0;
+  return q;
+}
 hipError_t launch_map_sweep(const MapArgs& a, const SweepPlan& p, int style, hipStream_t stream);
 
 // K-split layer-sweep kernels (bf16, d = 128, same plan): the two waves of a
 // target layer split the reduction (k <= 4); the second variant keeps the
-// matrix pipe busy across tiles (k = 2 or 4).
+// matrix pipe busy across tiles (k = 2 or 4).  The _raw forms read wk / wv and
+// write the packed images.
 bool map_ks_supported(int k, int64_t T, int64_t tgt_rows, bool slots, bool tgt_rope);
 hipError_t launch_map_ks(const MapArgs& a, const SweepPlan& p, int style, hipStream_t stream);
+hipError_t launch_map_ks_raw(const MapArgs& a, const SweepPlan& p, int style, hipStream_t stream);
 bool map_ks2_supported(int k, int64_t T, int64_t tgt_rows, bool slots, bool tgt_rope);
 hipError_t launch_map_ks2(const MapArgs& a, const SweepPlan& p, int style, hipStream_t stream);
+hipError_t launch_map_ks2_raw(const MapArgs& a, const SweepPlan& p, int style, hipStream_t stream);
 
 // Cross-head map (bf16, d = 64 or 128): strip pass, map packing and the
 // matrix-core product (kvx_xhead.hip).

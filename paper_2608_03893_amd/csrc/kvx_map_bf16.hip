@@ -36,74 +36,15 @@
 // target rotation touch the same 16 planes of a token in a lane, so with equal
 // RoPE on both sides the coefficients are loaded once per tile.
 #include "kvx_internal.h"
+#include "kvx_wload.h"
 
 #include <hip/hip_fp16.h>
 
 namespace kvx {
 namespace {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
 constexpr int D = 128;
 constexpr int HALF = 64;
-
-__device__ __forceinline__ float lo_bf16(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  __bf16 a = (__bf16)lo;
-  __bf16 b = (__bf16)hi;
-  return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
-}
-
-__device__ __forceinline__ bf16x8_t as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8_t, u); }
-
-// Inverse rotation of plane (u, v) by the angle whose (cos, sin) is the fp16
-// pair cs.  fma(x, y, 0) keeps the fp16 operand inside a mixed-precision FMA.
-__device__ __forceinline__ void strip(float& u, float& v, uint32_t cs) {
-  const __half2 h = __builtin_bit_cast(__half2, cs);
-  const float c = __low2float(h), s = __high2float(h);
-  const float u0 = u, v0 = v;
-  u = __builtin_fmaf(u0, c, __builtin_fmaf(v0, s, 0.0f));
-  v = __builtin_fmaf(v0, c, -__builtin_fmaf(u0, s, 0.0f));
-}
-
-// Forward rotation of plane (u, v) by the angle whose (cos, sin) is cs.
-__device__ __forceinline__ void rot_fwd16(float& u, float& v, uint32_t cs) {
-  const __half2 h = __builtin_bit_cast(__half2, cs);
-  const float c = __low2float(h), s = __high2float(h);
-  const float u0 = u, v0 = v;
-  u = __builtin_fmaf(u0, c, -__builtin_fmaf(v0, s, 0.0f));
-  v = __builtin_fmaf(v0, c, __builtin_fmaf(u0, s, 0.0f));
-}
-
-// Strip 8 planes whose first channels are packed in a and second channels in
-// b (half-split layout: channels j and j+64 in matching positions).
-__device__ __forceinline__ void strip_halfsplit(uint4& a, uint4& b, const uint32_t* cs) {
-  uint32_t* pa = reinterpret_cast<uint32_t*>(&a);
-  uint32_t* pb = reinterpret_cast<uint32_t*>(&b);
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    float u0 = lo_bf16(pa[w]), u1 = hi_bf16(pa[w]);
-    float v0 = lo_bf16(pb[w]), v1 = hi_bf16(pb[w]);
-    strip(u0, v0, cs[2 * w]);
-    strip(u1, v1, cs[2 * w + 1]);
-    pa[w] = pack2(u0, u1);
-    pb[w] = pack2(v0, v1);
-  }
-}
-
-// Strip the 4 interleaved planes (2m, 2m+1) held in one 8-channel group.
-__device__ __forceinline__ void strip_interleaved(uint4& a, const uint32_t* cs) {
-  uint32_t* pa = reinterpret_cast<uint32_t*>(&a);
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    float u = lo_bf16(pa[w]), v = hi_bf16(pa[w]);
-    strip(u, v, cs[w]);
-    pa[w] = pack2(u, v);
-  }
-}
 
 // ------------------------------------------------------------ packed map image
 // For one task the LDS image of W^T is dense: [128 accumulator rows rho][k*128
@@ -226,15 +167,40 @@ void map_w_kernel(const MapArgs a) {
   const int64_t t_begin = (int64_t)range * a.range_len;
   const int64_t t_end = t_begin + a.range_len < T ? t_begin + a.range_len : T;
 
-  // ---- stage W^T and the bias (content space, NULL = zero) in LDS
-  stage_wt<K, NT>(Wt, reinterpret_cast<const uint16_t*>(a.wpack) +
-                          (((int64_t)l * a.H + h) * 2 + kv) * (int64_t)D * KD, tid);
+  // ---- stage W^T and the bias (content space, NULL = zero) in LDS: W as given,
+  // transposed on the way, or its packed image
+  uint16_t* img = reinterpret_cast<uint16_t*>(a.wpack) + (((int64_t)l * a.H + h) * 2 + kv) * (int64_t)D * KD;
+  if (a.raw_w) {
+    const uint16_t* W = reinterpret_cast<const uint16_t*>(kv ? a.wv : a.wk) +
+                        ((int64_t)l * a.H + h) * (int64_t)KD * D;
+    constexpr int PER = 512 / NT;   // 4 x 8 pieces of a source layer's map per thread
+    uint4 r[PER][4];
+#pragma unroll
+    for (int n = 0; n < PER; ++n) load_piece<D>(W, tid + n * NT, r[n]);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+      for (int n = 0; n < PER; ++n) {
+        uint4 q[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[j] = r[n][j];
+        if (i + 1 < K) load_piece<D>(W + (i + 1) * D * D, tid + n * NT, r[n]);
+        store_piece<D, KD * 2>(reinterpret_cast<char*>(Wt) + i * 256, tid + n * NT, q);
+      }
+  } else {
+    stage_wt<K, NT>(Wt, img, tid);
+  }
   {
     const uint16_t* bias = reinterpret_cast<const uint16_t*>(kv ? a.bv : a.bk);
     if (tid < D)
       Bs[tid] = bias != nullptr ? lo_bf16(bias[((int64_t)l * a.H + h) * D + tid]) : 0.0f;
   }
   __syncthreads();
+  // the first range leaves the packed image for later calls
+  if (a.raw_w && range == 0) {
+    for (int n = tid; n < D * KD / 8; n += NT)
+      reinterpret_cast<uint4*>(img)[n] = reinterpret_cast<const uint4*>(Wt)[n];
+  }
 
   uint16_t* out = reinterpret_cast<uint16_t*>(a.tgt) + (((int64_t)l * 2 + kv) * a.H + h) * a.tgt_rows * D;
   const uint32_t* cs_s = reinterpret_cast<const uint32_t*>(a.cs16);

@@ -54,6 +54,14 @@
 #include "kvx_asm.h"
 #include "kvx_bf16.h"
 #include "kvx_internal.h"
+#include "kvx_wload.h"
+
+// This source is compiled twice: for the packed images of an earlier call, and
+// (KVX_RAW_MAPS 1) for maps read as given, whose packed images it writes.  One
+// kernel with both loads ran its tiles 1-2% slower.
+#ifndef KVX_RAW_MAPS
+#define KVX_RAW_MAPS 0
+#endif
 
 namespace kvx {
 namespace {
@@ -80,7 +88,8 @@ struct GeoK2 {
   static constexpr int cap(int n, int m) { return n < m ? n : m; }
   static constexpr int NK = cap((LDS_MAX - XCH) / KSTAGE, 4);   // stages, key units
   static constexpr int NV = cap((LDS_MAX - XCH) / VSTAGE, 5);   // stages, value units
-  static constexpr int LDS = XCH + (NK * KSTAGE > NV * VSTAGE ? NK * KSTAGE : NV * VSTAGE);
+  static constexpr int RING = XCH + (NK * KSTAGE > NV * VSTAGE ? NK * KSTAGE : NV * VSTAGE);
+  static constexpr int LDS = RING > 4 * kWRing || !KVX_RAW_MAPS ? RING : 4 * kWRing;
   static constexpr bool fits = (K == 2 || K == 4) && NK >= 3 && NV >= 3 && LDS <= LDS_MAX;
 };
 
@@ -219,6 +228,7 @@ struct Ks2Ctx {
   int lane, wave, c, row, sl;
   int64_t t_begin, t_end;
   int n_tiles;
+  bool first;   // the slot with its layers' first tokens writes the packed maps
 };
 
 template <int N>
@@ -318,23 +328,28 @@ __device__ __forceinline__ void ks2_unit(const MapArgs& a, uint32_t lds0, const 
   f32x4_t bias[4];   // owned blocks 2 OH, 2 OH + 1, 4 + 2 OH, 5 + 2 OH
   {
     const int l = a.l0 + lw;
-    const uint16_t* img = reinterpret_cast<const uint16_t*>(a.wpack) +
-                          (((int64_t)l * a.H + h) * 2 + KV) * (int64_t)D * (K * D);
+    const int64_t task = (int64_t)l * a.H + h;
+    if constexpr (KVX_RAW_MAPS) {
+      load_map_raw<SPLIT, Z0, ZH>(wf, reinterpret_cast<const uint16_t*>(KV ? a.wv : a.wk) + task * (K * D * D),
+                                  K * D * ROWB, lds0 + (uint32_t)(wave * kWRing), lane);
+    } else {
+      const uint16_t* img = reinterpret_cast<const uint16_t*>(a.wpack) + (task * 2 + KV) * (int64_t)D * (K * D);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const uint16_t* r0 = img + (int64_t)(16 * b + row) * (K * D);
+      for (int b = 0; b < 8; ++b) {
+        const uint16_t* r0 = img + (int64_t)(16 * b + row) * (K * D);
 #pragma unroll
-      for (int zz = 0; zz < ZH; ++zz) {
-        if (SPLIT) {
-          // the map rows of input features 16 s + 4 c .. + 3 of source u and
-          // of their RoPE partners 64 later: halves of chunks q and q + 8
-          const int z = Z0 + zz, u = z >> 2, s = z & 3;
-          const int q1 = 16 * u + 2 * s + (c >> 1);
-          const uint2 lo = *reinterpret_cast<const uint2*>(r0 + 8 * (q1 ^ row) + 4 * (c & 1));
-          const uint2 hi = *reinterpret_cast<const uint2*>(r0 + 8 * ((q1 + 8) ^ row) + 4 * (c & 1));
-          wf[b][zz] = (u32x4_t){lo.x, lo.y, hi.x, hi.y};
-        } else {
-          wf[b][zz] = *reinterpret_cast<const u32x4_t*>(r0 + 8 * ((4 * (Z0 + zz) + c) ^ row));
+        for (int zz = 0; zz < ZH; ++zz) {
+          if (SPLIT) {
+            // the map rows of input features 16 s + 4 c .. + 3 of source u and
+            // of their RoPE partners 64 later: halves of chunks q and q + 8
+            const int z = Z0 + zz, u = z >> 2, s = z & 3;
+            const int q1 = 16 * u + 2 * s + (c >> 1);
+            const uint2 lo = *reinterpret_cast<const uint2*>(r0 + 8 * (q1 ^ row) + 4 * (c & 1));
+            const uint2 hi = *reinterpret_cast<const uint2*>(r0 + 8 * ((q1 + 8) ^ row) + 4 * (c & 1));
+            wf[b][zz] = (u32x4_t){lo.x, lo.y, hi.x, hi.y};
+          } else {
+            wf[b][zz] = *reinterpret_cast<const u32x4_t*>(r0 + 8 * ((4 * (Z0 + zz) + c) ^ row));
+          }
         }
       }
     }
@@ -357,6 +372,7 @@ __device__ __forceinline__ void ks2_unit(const MapArgs& a, uint32_t lds0, const 
   // The map and bias loads are the compiler's own: wait for them here, with a
   // wait it knows of, so that it inserts none inside the tile loop.
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+  if (KVX_RAW_MAPS) __syncthreads();   // every wave is done with its staging ring: LDS becomes the stage ring
 
   // ---- per-lane offsets that do not change from tile to tile
   // source row loads: load g of a slot fetches tokens 4 g .. 4 g + 3; lane ->
@@ -600,6 +616,10 @@ __device__ __forceinline__ void ks2_unit(const MapArgs& a, uint32_t lds0, const 
   }
   vm_wait_c<(NS - 2) * S::NL>();               // tile 0 is in LDS
   __syncthreads();
+  if (KVX_RAW_MAPS && q.first && mine)
+    store_map_image<SPLIT, Z0, ZH, K>(wf, reinterpret_cast<uint16_t*>(a.wpack) +
+                                              (((int64_t)(a.l0 + lw) * a.H + h) * 2 + KV) * (int64_t)D * (K * D),
+                                      lane);
   {
     const uint32_t sb = stage_base(0);
     if (KEYS) {
@@ -781,47 +801,21 @@ void map_ks2_kernel(const MapArgs a, const Ks2Plan kp) {
 
   const int slot = blockIdx.x >> 3;   // CU slot within the XCD (0 .. 31)
   for (int unit = blockIdx.x & 7; unit < p.n_units; unit += 8) {
-    const int g = unit / (2 * a.H);
-    const int rem = unit % (2 * a.H);
-    int kv, h;
-    if (a.H % 8 == 0) {
-      kv = (rem >> 3) & 1;
-      h = (rem & 7) | ((rem >> 4) << 3);
-    } else {
-      kv = rem & 1;
-      h = rem >> 1;
-    }
-    int g0, g_n;
-    if (g < p.full_groups) {
-      g0 = 64 * g;
-      g_n = 64;
-    } else {
-      g0 = 64 * p.full_groups;
-      g_n = 0;
-      for (int r = 0; r < p.n_rest; ++r) {
-        if (r == g - p.full_groups) g_n = p.rest_len[r];
-        else if (r < g - p.full_groups) g0 += p.rest_len[r];
-      }
-    }
-    const int pairs = (g_n + 1) / 2;
-    const int parts = 32 / pairs;
-    const int pair = slot % pairs;
-    const int part = slot / pairs;
-    const int64_t per = ((int64_t)a.T + parts - 1) / parts;
-    const int64_t part_len = (per + MT - 1) / MT * MT;
-    q.t_begin = (int64_t)part * part_len;
-    if (part >= parts || q.t_begin >= a.T) continue;   // same decision in every thread
-    q.t_end = q.t_begin + part_len < a.T ? q.t_begin + part_len : a.T;
+    const SweepUnit u = sweep_unit_of(p, unit, slot, a.H, a.T, MT);
+    if (u.t_end <= u.t_begin) continue;   // same decision in every thread
+    q.t_begin = u.t_begin;
+    q.t_end = u.t_end;
+    q.first = u.first;
     q.n_tiles = (int)((q.t_end - q.t_begin + MT - 1) / MT);
-    const bool has1 = 2 * pair + 1 < g_n;
-    const int l_a = g0 + kp.order[g0 + 2 * pair];
-    const int l_b = has1 ? g0 + kp.order[g0 + 2 * pair + 1] : l_a;
-    if (kv == 0) {
-      if (kh == 0) ks2_unit<K, STYLE, SLOTS, TGT, 0, 0>(a, lds0, q, h, l_a, l_b, has1);
-      else ks2_unit<K, STYLE, SLOTS, TGT, 0, 1>(a, lds0, q, h, l_a, l_b, has1);
+    const bool has1 = 2 * u.pair + 1 < u.g_n;
+    const int l_a = u.g0 + kp.order[u.g0 + 2 * u.pair];
+    const int l_b = has1 ? u.g0 + kp.order[u.g0 + 2 * u.pair + 1] : l_a;
+    if (u.kv == 0) {
+      if (kh == 0) ks2_unit<K, STYLE, SLOTS, TGT, 0, 0>(a, lds0, q, u.h, l_a, l_b, has1);
+      else ks2_unit<K, STYLE, SLOTS, TGT, 0, 1>(a, lds0, q, u.h, l_a, l_b, has1);
     } else {
-      if (kh == 0) ks2_unit<K, STYLE, SLOTS, TGT, 1, 0>(a, lds0, q, h, l_a, l_b, has1);
-      else ks2_unit<K, STYLE, SLOTS, TGT, 1, 1>(a, lds0, q, h, l_a, l_b, has1);
+      if (kh == 0) ks2_unit<K, STYLE, SLOTS, TGT, 1, 0>(a, lds0, q, u.h, l_a, l_b, has1);
+      else ks2_unit<K, STYLE, SLOTS, TGT, 1, 1>(a, lds0, q, u.h, l_a, l_b, has1);
     }
   }
 }
@@ -850,13 +844,14 @@ hipError_t launch_ks2style(const MapArgs& a, const Ks2Plan& p, int style, hipStr
 }
 
 template <int K>
-bool ks2_fits(bool slots, bool tgt) {
+[[maybe_unused]] bool ks2_fits(bool slots, bool tgt) {
   return slots ? (tgt ? GeoK2<K, true, true>::fits : GeoK2<K, true, false>::fits)
                : (tgt ? GeoK2<K, false, true>::fits : GeoK2<K, false, false>::fits);
 }
 
 }  // namespace
 
+#if !KVX_RAW_MAPS
 bool map_ks2_supported(int k, int64_t T, int64_t tgt_rows, bool slots, bool tgt_rope) {
   // byte offsets within a plane, and of the tiles loaded ahead past its end,
   // must fit the 32-bit buffer offsets; the stages must fit the LDS
@@ -867,6 +862,7 @@ bool map_ks2_supported(int k, int64_t T, int64_t tgt_rows, bool slots, bool tgt_
     default: return false;   // a wave's reduction half would split a source layer
   }
 }
+#endif
 
 static void ks2_pair_order(const uint8_t* idx, int k, int g0, int g_n, uint8_t* order) {
   // sh[i][j]: sources of layer j that layer i also lists (the slots of a
@@ -917,7 +913,12 @@ static void ks2_pair_order(const uint8_t* idx, int k, int g0, int g_n, uint8_t* 
     if (!used[c]) order[g0 + n++] = (uint8_t)c;
 }
 
-hipError_t launch_map_ks2(const MapArgs& a, const SweepPlan& sp, int style, hipStream_t stream) {
+#if KVX_RAW_MAPS
+hipError_t launch_map_ks2_raw(
+#else
+hipError_t launch_map_ks2(
+#endif
+    const MapArgs& a, const SweepPlan& sp, int style, hipStream_t stream) {
   if (a.T == 0 || a.nl == 0) return hipSuccess;
   if (a.nl > kMaxIdx / 2) return hipErrorInvalidValue;
   Ks2Plan p;

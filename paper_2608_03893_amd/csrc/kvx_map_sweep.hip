@@ -463,49 +463,18 @@ void map_sweep_kernel(const MapArgs a, const SweepPlan p) {
   const int slot = blockIdx.x >> 3;   // CU slot within the XCD (0 .. 31)
   q.T = a.T;
 
-  // Unit u -> (group, K|V, head).  Within a group, keys cost more vector work
-  // than values (two rotations), so when the units of one kind divide evenly
-  // over the eight XCDs every XCD takes both kinds.
   for (int unit = blockIdx.x & 7; unit < p.n_units; unit += 8) {
-    const int g = unit / (2 * a.H);
-    const int rem = unit % (2 * a.H);
-    int kv, h;
-    if (a.H % 8 == 0) {
-      kv = (rem >> 3) & 1;
-      h = (rem & 7) | ((rem >> 4) << 3);
-    } else {
-      kv = rem & 1;
-      h = rem >> 1;
-    }
-    int g0, g_n;
-    if (g < p.full_groups) {
-      g0 = 64 * g;
-      g_n = 64;
-    } else {
-      g0 = 64 * p.full_groups;
-      g_n = 0;
-      for (int r = 0; r < p.n_rest; ++r) {
-        if (r == g - p.full_groups) g_n = p.rest_len[r];
-        else if (r < g - p.full_groups) g0 += p.rest_len[r];
-      }
-    }
-    // this CU's layer pair and token part (pairs * parts = 32)
-    const int pairs = (g_n + 1) / 2;
-    const int parts = 32 / pairs;
-    const int pair = slot % pairs;
-    const int part = slot / pairs;
-    const int64_t per = (q.T + parts - 1) / parts;
-    const int64_t part_len = (per + MT - 1) / MT * MT;
-    q.t_begin = (int64_t)part * part_len;
-    if (part >= parts || q.t_begin >= q.T) continue;   // same decision in every thread
-    q.t_end = q.t_begin + part_len < q.T ? q.t_begin + part_len : q.T;
+    const SweepUnit u = sweep_unit_of(p, unit, slot, a.H, a.T, MT);
+    if (u.t_end <= u.t_begin) continue;   // same decision in every thread
+    q.t_begin = u.t_begin;
+    q.t_end = u.t_end;
     q.n_tiles = (int)((q.t_end - q.t_begin + MT - 1) / MT);
-    const int ll0 = g0 + 2 * pair;          // first layer of the pair, relative to l0
-    const bool has1 = 2 * pair + 1 < g_n;
-    if (kv == 0)
-      sweep_unit<K, STYLE, SLOTS, 0, 2>(a, q, X, Bs, h, ll0, has1);
+    const int ll0 = u.g0 + 2 * u.pair;          // first layer of the pair, relative to l0
+    const bool has1 = 2 * u.pair + 1 < u.g_n;
+    if (u.kv == 0)
+      sweep_unit<K, STYLE, SLOTS, 0, 2>(a, q, X, Bs, u.h, ll0, has1);
     else
-      sweep_unit<K, STYLE, SLOTS, 1, 2>(a, q, X, Bs, h, ll0, has1);
+      sweep_unit<K, STYLE, SLOTS, 1, 2>(a, q, X, Bs, u.h, ll0, has1);
   }
 }
 
@@ -525,14 +494,19 @@ hipError_t launch_sstyle(const MapArgs& a, const SweepPlan& p, int style, hipStr
 
 }  // namespace
 
-SweepPlan plan_sweep(int nl, int H, int64_t /*T*/) {
+SweepPlan plan_sweep(int nl, int H, int64_t T) {
   SweepPlan p{};
   p.full_groups = nl / 64;
   int r = nl % 64;
   for (int bit = 32; bit >= 1; bit >>= 1)
     if (r & bit) p.rest_len[p.n_rest++] = bit;
   p.n_groups = p.full_groups + p.n_rest;
-  p.n_units = p.n_groups * H * 2;
+  // a head count that does not divide over the eight XCDs: cut the tokens too
+  p.segs = 1;
+  while (H * p.segs % 8 != 0) p.segs *= 2;
+  const int64_t seg_len = T / p.segs;
+  if (p.segs > 1 && seg_len * nl < (int64_t)kSegTiles * 1024 * p.n_groups) p.segs = 1;
+  p.n_units = p.n_groups * H * p.segs * 2;
   return p;
 }
 

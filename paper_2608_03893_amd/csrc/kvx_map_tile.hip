@@ -17,6 +17,7 @@
 // 16-byte stores of which the four lanes of a token cover 64 bytes.
 #include "kvx_bf16.h"
 #include "kvx_internal.h"
+#include "kvx_wload.h"
 
 #include <type_traits>
 
@@ -37,55 +38,6 @@ struct TileGeo {
   static constexpr int SLOTB = D * ROWB;       // bytes of one source layer's map
   static constexpr int PIECES = (D / 4) * (D / 8);   // 4 x 8 pieces of a source layer's map
 };
-
-// Position of 16-byte chunk q of map row rho: the 16 rows of a fragment read
-// fall on distinct LDS banks (row bytes: one or half a sweep of the 64 banks).
-template <int D>
-__device__ __forceinline__ int chunk_pos(int q, int rho) {
-  return D == 128 ? q ^ (rho & 15) : q ^ ((rho >> 1) & 7);
-}
-
-// One 4 x 8 piece of a source layer's map: input rows 4 kg .. + 3, output
-// channels 8 ng .. + 7.  The lanes of half a wave take 8 kg and 4 ng, whose
-// 8-byte LDS writes of one channel fall on distinct banks; the wave reads
-// whole 128-byte lines.
-template <int D>
-__device__ __forceinline__ void piece_of(int n, int& kg, int& ng) {
-  if (D == 128) {
-    kg = (n & 7) | ((n >> 7) << 3);
-    ng = ((n >> 3) & 3) | (((n >> 5) & 3) << 2);
-  } else {
-    kg = (n & 7) | ((n >> 6) << 3);
-    ng = ((n >> 3) & 3) | (((n >> 5) & 1) << 2);
-  }
-}
-
-template <int D>
-__device__ __forceinline__ void load_piece(const uint16_t* __restrict__ w, int n, uint4 (&r)[4]) {
-  int kg, ng;
-  piece_of<D>(n, kg, ng);
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    r[j] = *reinterpret_cast<const uint4*>(w + (4 * kg + j) * D + 8 * ng);
-}
-
-template <int D>
-__device__ __forceinline__ void store_piece(char* lds, int n, const uint4 (&r)[4]) {
-  using G = TileGeo<D>;
-  int kg, ng;
-  piece_of<D>(n, kg, ng);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int rho = 16 * (2 * (ng >> 2) + (e >> 2)) + 4 * (ng & 3) + (e & 3);
-    const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-    uint32_t w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = (&r[j].x)[e >> 1];
-    const uint2 v = make_uint2(__builtin_amdgcn_perm(w[1], w[0], sel),
-                               __builtin_amdgcn_perm(w[3], w[2], sel));
-    *reinterpret_cast<uint2*>(lds + rho * G::ROWB + 16 * chunk_pos<D>(kg >> 1, rho) + 8 * (kg & 1)) = v;
-  }
-}
 
 __device__ __forceinline__ void rot_inv32(float& u, float& v, float2 cs) {
   const float u0 = u, v0 = v;
@@ -274,7 +226,7 @@ void map_kernel(const MapArgs a, const TilePlan p) {
   int64_t cs_t0 = -1;
   if (stager) load_piece<D>(w_of(cur, 0), tid, wr);
   load_x(cur, 0, nx);
-  if (stager) store_piece<D>(smem, tid, wr);
+  if (stager) store_piece<D, G::ROWB>(smem, tid, wr);
   // positions one and two source layers ahead; past the end they repeat the last
   Item i1 = cur;
   int k1 = 0;
@@ -313,7 +265,7 @@ void map_kernel(const MapArgs a, const TilePlan p) {
         for (int s = 0; s < S; ++s) x[tb][s] = nx[tb][s];
       // the next source layer's map into the stage of the previous one, then
       // the loads after it
-      if (stager) store_piece<D>(smem + (st ^ 1) * G::SLOTB, tid, wr);
+      if (stager) store_piece<D, G::ROWB>(smem + (st ^ 1) * G::SLOTB, tid, wr);
       load_x(i1, k1, nx);
       advance(i1, k1, n1);
       if (stager) load_piece<D>(w_of(i1, k1), tid, wr);
@@ -403,7 +355,7 @@ void map_resident_kernel(const MapArgs a, const TilePlan p) {
       const int i = m / G::PIECES, q = m % G::PIECES;
       uint4 r[4];
       load_piece<D>(w + i * (int64_t)(D * D), q, r);
-      store_piece<D>(wsm + i * G::SLOTB, q, r);
+      store_piece<D, G::ROWB>(wsm + i * G::SLOTB, q, r);
     }
   }
   const uint16_t* bias = reinterpret_cast<const uint16_t*>(it.kv ? a.bv : a.bk);
