@@ -1390,18 +1390,24 @@ __global__ __launch_bounds__(256) void probe_kernel(const FitArgs a) {
 
 // ------------------------------------------------------------------ top-k
 
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ r2, int L_s, int L_t,
-                                                   int H, int k, int32_t* __restrict__ out) {
-  const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= L_t) return;
+// Mean R2 of source layer s for target layer l, summed in (head, K|V) order.
+__device__ __forceinline__ double topk_score(const float* __restrict__ r2, int s, int l, int L_t,
+                                             int H) {
+  double v = 0.0;
+  for (int h = 0; h < H; ++h)
+    for (int kv = 0; kv < 2; ++kv) v += (double)r2[(((int64_t)s * L_t + l) * H + h) * 2 + kv];
+  return v / (double)(2 * H);
+}
+
+// The top k by inserting source layers in order: an equal score keeps the
+// earlier index ahead, a NaN is neither passed nor passes.
+template <class Score>
+__device__ void topk_insert(Score score, int L_s, int k, int32_t* __restrict__ out) {
   int best[32];
   double bs[32];
   int n = 0;
   for (int s = 0; s < L_s; ++s) {
-    double v = 0.0;
-    for (int h = 0; h < H; ++h)
-      for (int kv = 0; kv < 2; ++kv) v += (double)r2[(((int64_t)s * L_t + l) * H + h) * 2 + kv];
-    v /= (double)(2 * H);
+    const double v = score(s);
     // insert into the descending list; an equal score keeps the earlier
     // (lower) source index ahead
     int pos = n;
@@ -1424,7 +1430,49 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ r2,
       best[q] = best[q - 1];
       best[q - 1] = tmp;
     }
-  for (int i = 0; i < k; ++i) out[(int64_t)l * k + i] = best[i];
+  for (int i = 0; i < k; ++i) out[i] = best[i];
+}
+
+constexpr int TOPK_LS = 1024;   // scores a workgroup keeps in LDS
+
+// One wave per target layer: a lane per source layer forms the scores, counts
+// the scores ahead of its own (larger, or equal with a lower index) and takes
+// its place in ascending source order.  Bound by the latency of the score
+// loads: 40 x 64 layers, 8 heads 78 us with one thread per target layer.
+__global__ __launch_bounds__(64) void topk_kernel(const float* __restrict__ r2, int L_s, int L_t,
+                                                  int H, int k, int32_t* __restrict__ out) {
+  __shared__ double sc[TOPK_LS];
+  const int l = blockIdx.x, lane = threadIdx.x;
+  out += (int64_t)l * k;
+  if (L_s > TOPK_LS) {
+    if (lane == 0) topk_insert([&](int s) { return topk_score(r2, s, l, L_t, H); }, L_s, k, out);
+    return;
+  }
+  bool nan = false;
+  for (int s = lane; s < L_s; s += 64) {
+    const double v = topk_score(r2, s, l, L_t, H);
+    sc[s] = v;
+    nan |= v != v;
+  }
+  __syncthreads();
+  if (__any(nan)) {
+    if (lane == 0) topk_insert([&](int s) { return sc[s]; }, L_s, k, out);
+    return;
+  }
+  int taken = 0;   // selected source layers below this group of 64
+  for (int s0 = 0; s0 < L_s; s0 += 64) {
+    const int s = s0 + lane;
+    bool sel = s < L_s;
+    if (sel) {
+      const double v = sc[s];
+      int ahead = 0;
+      for (int q = 0; q < L_s; ++q) ahead += sc[q] > v || (sc[q] == v && q < s);
+      sel = ahead < k;
+    }
+    const uint64_t m = __ballot(sel);
+    if (sel) out[taken + __popcll(m & ((1ull << lane) - 1))] = s;
+    taken += __popcll(m);
+  }
 }
 
 }  // namespace
@@ -1501,7 +1549,7 @@ hipError_t launch_fit(FitArgs a, bool prep, hipStream_t stream) {
 
 hipError_t launch_topk(const float* r2, int L_s, int L_t, int H, int k, int32_t* out,
                        hipStream_t stream) {
-  hipLaunchKernelGGL(topk_kernel, dim3((L_t + 255) / 256), dim3(256), 0, stream, r2, L_s, L_t, H,
+  hipLaunchKernelGGL(topk_kernel, dim3(L_t), dim3(64), 0, stream, r2, L_s, L_t, H,
                      k, out);
   return hipGetLastError();
 }

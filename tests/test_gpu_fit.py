@@ -268,3 +268,28 @@ def test_planes_ready_reuses_the_planes(gpu_kvx):
         assert torch.equal(a, b) and torch.equal(a, e)
     assert torch.equal(r2_full, r2_after_fit)
     log(f"[parity] planes-ready fit and probe bit-identical to full calls (N={N})")
+
+
+@pytest.mark.parametrize("L_s,L_t,k", [(1, 1, 1), (5, 3, 5), (64, 2, 7), (65, 3, 32), (200, 1, 9), (1030, 2, 4)])
+def test_topk_ties_and_nan(gpu_kvx, L_s, L_t, k):
+    """Scores from a few values (many ties), then with NaN among them: the
+    insertion order of the documented rule, replayed on the host."""
+    g = torch.Generator().manual_seed(L_s)
+    r2 = torch.randint(0, 4, (L_s, L_t, 1, 2), generator=g).float() / 4
+    def insert(v):
+        best = []
+        for s in range(L_s):
+            pos = len(best)
+            while pos > 0 and v[best[pos - 1]] < v[s]:
+                pos -= 1
+            if pos < k:
+                best.insert(pos, s)
+                del best[k:]
+        return sorted(best)
+    for nan in (False, True):
+        if nan:
+            r2[L_s // 2] = float("nan")
+        idx = gpu_kvx.select_topk(r2.to("cuda:0"), k).cpu().numpy()
+        v = r2.double().sum((2, 3)).numpy() / 2
+        want = np.array([insert(v[:, l]) for l in range(L_t)])
+        np.testing.assert_array_equal(idx, want)
