@@ -1,20 +1,30 @@
-// Map kernels for bf16 calls outside the packed-map kernels: more than four
+// Map kernel for bf16 calls outside the packed-map kernels: more than four
 // source layers, or head dimension 64.
 //
-// Both compute one (target layer, head, K|V) task on a tile of 256 tokens, 8
-// waves of 32 tokens, as C^T = W^T X^T on v_mfma_f32_16x16x32_bf16 (Eq.
-// ridge_kv, Sec. 3.1).  A wave loads its tokens' rows of each selected source
-// layer straight into registers, one source layer ahead, strips the source
-// RoPE from keys there (Sec. 3.3, fp32 coefficients, one rounding) and feeds
-// each row fragment to all D / 16 output blocks.  W is read as given and
-// transposed on its way into LDS (4 input rows x 8 output channels per
-// thread), so no packed copy of it is needed.
+// One workgroup per CU works through its items, each one (target layer, head,
+// K|V) task on a tile of 256 tokens, 8 waves of 32 tokens, as C^T = W^T X^T on
+// v_mfma_f32_16x16x32_bf16 (Eq. ridge_kv, Sec. 3.1).  Rows and maps stream
+// through LDS in positions of 64 reduction channels (two steps, whole RoPE
+// planes of a source layer), loaded straight into LDS three positions ahead,
+// across items.  Rows are private to their wave, which strips the source RoPE
+// from its fragments (Sec. 3.3, fp32 coefficients, one rounding) and feeds each
+// to all D / 16 output blocks.  W is read as given: transposed LDS reads give
+// the map fragments.  Outputs go through LDS, so that stores cover whole rows.
+//
+// Why rows go through LDS: fragments loaded straight into registers (16 rows x
+// 64 bytes per instruction, neighbouring lanes in different rows) run at 18
+// bytes per clock and CU even out of L2 (9.7 TB/s over the chip); with 64
+// contiguous bytes per four neighbouring lanes the same loads reach 33 TB/s.
+// Bound by the key strip and the waits around the position barrier (matrix
+// pipe busy about 30%).  Qwen3-14B->32B shapes, k = 8, T = 8191: 3.29 ms (0.67
+// PFLOP/s; 4.35 ms with rows straight into registers and barriers per source
+// layer, 16.95 ms with 64-token tiles staged without a pipeline); head
+// dimension 64, 16 -> 28 layers, k = 4, T = 8192: 0.369 ms (0.415 and 0.667).
 //
 // Operand layout: lane L = 16 c + r supplies map row / token r and reduction
-// indices 8 c .. 8 c + 7 of a 32-wide step.  Map row 16 b + 4 c + i holds
-// output channel 32 (b / 2) + 8 c + 4 (b % 2) + i, so that a lane ends with
-// channels 32 x + 8 c .. + 7: both members of every RoPE plane it touches, and
-// 16-byte stores of which the four lanes of a token cover 64 bytes.
+// indices 8 c .. 8 c + 7 of a 32-wide step.  Map row 16 b + 4 c + i holds output
+// channel 16 b + 4 c + i: blocks b and b + D / 32 (half-split) or neighbouring
+// elements (interleaved) hold the members of a RoPE plane in one lane.
 #include "kvx_bf16.h"
 #include "kvx_internal.h"
 #include "kvx_wload.h"
@@ -26,17 +36,23 @@ namespace {
 
 constexpr int NTHR = 512;      // threads per workgroup
 constexpr int TB = 2;          // 16-token blocks per wave
-constexpr int BT = 8 * 16 * TB;   // tokens per tile
+constexpr int WT = 16 * TB;    // tokens per wave
+constexpr int BT = 8 * WT;     // tokens per tile
 
 template <int D>
 struct TileGeo {
   static constexpr int S = D / 32;             // reduction steps per source layer
+  static constexpr int PPS = S / 2;            // positions per source layer
   static constexpr int NB = D / 16;            // output blocks
   static constexpr int HALF = D / 2;
   static constexpr int PL = D / 8;             // RoPE planes of a token in a lane
-  static constexpr int ROWB = 2 * D;           // bytes of a map row in LDS
-  static constexpr int SLOTB = D * ROWB;       // bytes of one source layer's map
-  static constexpr int PIECES = (D / 4) * (D / 8);   // 4 x 8 pieces of a source layer's map
+  static constexpr int ROWB = 2 * D;           // bytes of a row of rows, maps and outputs
+  static constexpr int XB = WT * 128;          // a wave's rows of one position
+  static constexpr int WB = 64 * ROWB;         // the map rows of one position
+  static constexpr int XD = XB / 1024;         // loads of a wave per position: rows
+  static constexpr int WD = WB / 8192;         // and maps
+  static constexpr int NX = 3, NW = 4;         // positions in LDS: rows and maps
+  static constexpr int LDS = NX * 8 * XB + NW * WB;
 };
 
 __device__ __forceinline__ void rot_inv32(float& u, float& v, float2 cs) {
@@ -67,123 +83,143 @@ __device__ __forceinline__ void load_planes(const float2* __restrict__ table, in
   }
 }
 
-template <int D, int STYLE>
-__device__ __forceinline__ void strip_row(u32x4_t (&x)[TileGeo<D>::S], const float2 (&cs)[TileGeo<D>::PL]) {
+// Place of the 32-byte runs of map row m (see the map loads): rows 0..3 and
+// 8..11 of a fragment read differ in it (D = 64: beside the row's own half of
+// the banks).
+template <int D>
+__device__ __forceinline__ int map_swz(int m) {
+  return D == 128 ? (m & 3) + 4 * ((m >> 3) & 1) : ((m >> 1) & 1) + 2 * ((m >> 3) & 1);
+}
+
+// Strip the source RoPE from a token's fragments of position X.
+template <int D, int STYLE, int X>
+__device__ __forceinline__ void strip_pos(u32x4_t& x0, u32x4_t& x1, const float2 (&cs)[TileGeo<D>::PL]) {
   constexpr int S = TileGeo<D>::S;
-  if (STYLE == 0) {
 #pragma unroll
-    for (int s = 0; s < S / 2; ++s)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        uint32_t& a = reinterpret_cast<uint32_t*>(&x[s])[w];
-        uint32_t& b = reinterpret_cast<uint32_t*>(&x[s + S / 2])[w];
-        float u0 = lo_bf16(a), u1 = hi_bf16(a), v0 = lo_bf16(b), v1 = hi_bf16(b);
-        rot_inv32(u0, v0, cs[8 * s + 2 * w]);
-        rot_inv32(u1, v1, cs[8 * s + 2 * w + 1]);
-        a = pack2(u0, u1);
-        b = pack2(v0, v1);
-      }
-  } else {
-#pragma unroll
-    for (int s = 0; s < S; ++s)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        uint32_t& a = reinterpret_cast<uint32_t*>(&x[s])[w];
-        float u = lo_bf16(a), v = hi_bf16(a);
-        rot_inv32(u, v, cs[4 * s + w]);
-        a = pack2(u, v);
-      }
+  for (int w = 0; w < 4; ++w) {
+    float u0 = lo_bf16(x0[w]), u1 = hi_bf16(x0[w]), v0 = lo_bf16(x1[w]), v1 = hi_bf16(x1[w]);
+    if (STYLE == 0) {
+      rot_inv32(u0, v0, cs[8 * X + 2 * w]);
+      rot_inv32(u1, v1, cs[8 * X + 2 * w + 1]);
+    } else {
+      rot_inv32(u0, u1, cs[4 * X + w]);
+      rot_inv32(v0, v1, cs[4 * (X + S / 2) + w]);
+    }
+    x0[w] = pack2(u0, u1);
+    x1[w] = pack2(v0, v1);
   }
 }
 
-// Bias, target RoPE (keys), rounding and store of one token's outputs.
+// Bias, target RoPE (keys) and rounding of one token's outputs: channels
+// 16 b + 4 c .. + 3 in o[b].
 template <int D, int STYLE, bool KEYS>
 __device__ __forceinline__ void finish_row(const f32x4_t (&acc)[TileGeo<D>::NB],
                                            const uint16_t* __restrict__ bias,
                                            const float2* __restrict__ table, int64_t t, int c,
-                                           uint16_t* __restrict__ out, bool store) {
+                                           uint2 (&o)[TileGeo<D>::NB]) {
   using G = TileGeo<D>;
-  float y[G::S][8];
+  constexpr int NB = G::NB;
+  float y[NB][4];
 #pragma unroll
-  for (int x = 0; x < G::S; ++x)
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) y[x][e] = acc[2 * x + (e >> 2)][e & 3];
+    for (int e = 0; e < 4; ++e) y[b][e] = acc[b][e];
   if (bias != nullptr) {
 #pragma unroll
-    for (int x = 0; x < G::S; ++x) {
-      const uint4 b = *reinterpret_cast<const uint4*>(bias + 32 * x + 8 * c);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        y[x][2 * w] += lo_bf16((&b.x)[w]);
-        y[x][2 * w + 1] += hi_bf16((&b.x)[w]);
-      }
+    for (int b = 0; b < NB; ++b) {
+      const uint2 v = *reinterpret_cast<const uint2*>(bias + 16 * b + 4 * c);
+      y[b][0] += lo_bf16(v.x);
+      y[b][1] += hi_bf16(v.x);
+      y[b][2] += lo_bf16(v.y);
+      y[b][3] += hi_bf16(v.y);
     }
   }
   if (KEYS) {
-    float2 cs[G::PL];
-    load_planes<D, STYLE>(table, t, c, cs);
+    // half-split: planes 16 b + 4 c + e of blocks b and b + NB / 2;
+    // interleaved: planes 8 b + 2 c + e / 2
+    const float4* q = reinterpret_cast<const float4*>(table + t * G::HALF);
     if (STYLE == 0) {
 #pragma unroll
-      for (int x = 0; x < G::S / 2; ++x)
+      for (int b = 0; b < NB / 2; ++b)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) rot_fwd32(y[x][e], y[x + G::S / 2][e], cs[8 * x + e]);
+        for (int e = 0; e < 4; e += 2) {
+          const float4 f = q[8 * b + 2 * c + e / 2];
+          rot_fwd32(y[b][e], y[b + NB / 2][e], make_float2(f.x, f.y));
+          rot_fwd32(y[b][e + 1], y[b + NB / 2][e + 1], make_float2(f.z, f.w));
+        }
     } else {
 #pragma unroll
-      for (int x = 0; x < G::S; ++x)
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) rot_fwd32(y[x][e], y[x][e + 1], cs[4 * x + e / 2]);
+      for (int b = 0; b < NB; ++b) {
+        const float4 f = q[4 * b + c];
+        rot_fwd32(y[b][0], y[b][1], make_float2(f.x, f.y));
+        rot_fwd32(y[b][2], y[b][3], make_float2(f.z, f.w));
+      }
     }
   }
-  if (store) {
 #pragma unroll
-    for (int x = 0; x < G::S; ++x)
-      *reinterpret_cast<uint4*>(out + 32 * x + 8 * c) =
-          make_uint4(pack2(y[x][0], y[x][1]), pack2(y[x][2], y[x][3]), pack2(y[x][4], y[x][5]),
-                     pack2(y[x][6], y[x][7]));
-  }
+  for (int b = 0; b < NB; ++b) o[b] = make_uint2(pack2(y[b][0], y[b][1]), pack2(y[b][2], y[b][3]));
 }
 
-// ------------------------------------------------------- streamed maps
-//
-// One workgroup per CU; the maps stream through two LDS stages, one source
-// layer at a time, and the pipeline runs on from item to item.  The 32 CUs of
-// an XCD work on 32 target layers of one (head, K|V) and token tile, so that
-// the tile's source rows are read into its L2 once.  Bound by the operand reads
-// from LDS (each map fragment feeds two matrix instructions) and by the loads
-// that share the vector memory pipe.  Qwen3-14B->32B shapes with k = 8, T =
-// 8191: 4.35 ms (0.51 PFLOP/s); the 64-token tiles that staged rows and maps
-// through LDS without a pipeline took 16.95 ms.
-
-// The items (head, token tile, K|V, target layer; layers fastest) are cut into
-// eight contiguous ranges, one per XCD.
+// The items (head, token group, K|V, tile, target layer; layers fastest) are cut
+// into eight contiguous ranges, one per XCD.  The 32 CUs of an XCD then work on
+// 32 target layers of one (head, K|V) and tile, whose source rows its L2 holds,
+// and the maps that the tiles read again and again are those of keys or of
+// values, which the last-level cache holds where it does not hold both (268 MB
+// at 64 layers, 8 heads, k = 8; 2% slower with K|V inside the tiles).
+// Token groups, 8 / gcd(8, heads) of them, give every XCD keys and values.
 struct TilePlan {
   int64_t items, per_xcd;
-  int32_t tiles, len;   // token tiles (ranges) and their length
+  int32_t tiles, per_group;   // 256-token tiles, and of a token group
 };
 
 struct Item {
-  int h, kv, ll;
-  int64_t t0;
+  int h, g, kv, t, ll;   // t: tile within token group g
 };
 
+__device__ __forceinline__ int group_tiles(const TilePlan& p, int g) {
+  const int left = p.tiles - g * p.per_group;
+  return left < p.per_group ? left : p.per_group;
+}
 __device__ __forceinline__ Item item_of(const MapArgs& a, const TilePlan& p, int64_t n) {
   Item it;
-  it.ll = (int)(n % a.nl);
-  n /= a.nl;
-  it.kv = (int)(n & 1);
-  n >>= 1;
-  it.t0 = (n % p.tiles) * p.len;
-  it.h = (int)(n / p.tiles);
+  const int64_t per_h = (int64_t)p.tiles * 2 * a.nl;
+  it.h = (int)(n / per_h);
+  n -= it.h * per_h;
+  const int64_t per_g = (int64_t)p.per_group * 2 * a.nl;
+  it.g = (int)(n / per_g);
+  n -= it.g * per_g;
+  const int64_t per_kv = (int64_t)group_tiles(p, it.g) * a.nl;
+  it.kv = n >= per_kv;
+  n -= it.kv ? per_kv : 0;
+  it.t = (int)(n / a.nl);
+  it.ll = (int)(n - (int64_t)it.t * a.nl);
   return it;
+}
+// The item `step` places on (no division: it runs between matrix instructions).
+__device__ __forceinline__ void item_add(const MapArgs& a, const TilePlan& p, Item& it, int step) {
+  it.ll += step;
+  while (it.ll >= a.nl) {
+    it.ll -= a.nl;
+    if (++it.t == group_tiles(p, it.g)) {
+      it.t = 0;
+      it.kv ^= 1;
+      if (it.kv == 0 && ++it.g * p.per_group >= p.tiles) {
+        it.g = 0;
+        ++it.h;
+      }
+    }
+  }
 }
 
 template <int D, int STYLE, bool SLOTS>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void map_kernel(const MapArgs a, const TilePlan p) {
   using G = TileGeo<D>;
-  constexpr int S = G::S, NB = G::NB;
-  __shared__ __attribute__((aligned(256))) char smem[2 * G::SLOTB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NB = G::NB, NX = G::NX, NW = G::NW, ND = G::XD + G::WD;
+  static_assert(G::LDS <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(1024))) char smem[G::LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane >> 4, row = lane & 15;
   const int64_t T = a.T;
   const int k = a.k;
@@ -194,62 +230,137 @@ void map_kernel(const MapArgs a, const TilePlan p) {
   int64_t n = x0 + (blockIdx.x >> 3);
   if (n >= end) return;   // same decision in every thread
 
-  auto w_of = [&](const Item& it, int i) __attribute__((always_inline)) -> const uint16_t* {
-    return reinterpret_cast<const uint16_t*>(it.kv ? a.wv : a.wk) +
-           (((int64_t)(a.l0 + it.ll) * a.H + it.h) * k + i) * (int64_t)(D * D);
+  // LDS: [stage][wave] rows, then [stage] maps
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_u32(smem));
+  const uint32_t xl = lds0 + (uint32_t)(wave * G::XB), wl = lds0 + (uint32_t)(NX * 8 * G::XB);
+  char* const xp = smem + wave * G::XB;
+
+  // Row loads: load g of a position fetches this wave's tokens 8 g .. 8 g + 7,
+  // 64 contiguous bytes per four lanes; 16-byte chunk q of token r (0..3: the
+  // step's channels, 4..7: those D / 2 later) at position q ^ (r / 2 % 8).
+  uint32_t vx[G::XD];
+#pragma unroll
+  for (int g = 0; g < G::XD; ++g) {
+    const int q = (lane & 7) ^ ((4 * g + (lane >> 4)) & 7);
+    vx[g] = (uint32_t)((WT * wave + 8 * g + (lane >> 3)) * G::ROWB + (q >> 2) * D + 16 * (q & 3));
+  }
+  // Map loads: the wave's WD kilobytes of a position's 64 map rows, row m at
+  // 2 D m bytes, 16-byte chunk q at position q ^ 2 f(m): the 32 bytes that half
+  // a wave reads of each of eight rows fall on distinct banks.
+  uint32_t vw[G::WD];
+#pragma unroll
+  for (int g = 0; g < G::WD; ++g) {
+    constexpr int RPL = 1024 / G::ROWB;    // rows per load
+    const int m = RPL * (8 * g + wave) + lane / (64 / RPL);
+    const int q = (lane % (64 / RPL)) ^ (2 * map_swz<D>(m));
+    vw[g] = (uint32_t)(((m & 31) + (m >> 5) * G::HALF) * G::ROWB + 16 * q);
+  }
+  // A position: source layer i of an item and 64 of its channels.
+  struct Pos {
+    int64_t n;
+    Item it;
+    int i, x;
   };
-  auto x_of = [&](const Item& it, int i) __attribute__((always_inline)) -> const uint16_t* {
-    return reinterpret_cast<const uint16_t*>(a.src) +
-           (((int64_t)a.idx[it.ll * k + i] * 2 + it.kv) * a.H + it.h) * T * D;
+  // The index list is read by words: bytes of the kernel arguments come by
+  // vector loads, whose wait drains the loads in flight (k = 8: 4.0 ms).
+  const uint32_t* const idx4 = reinterpret_cast<const uint32_t*>(a.idx);
+  auto t0_of = [&](const Item& it) __attribute__((always_inline)) -> int64_t {
+    return ((int64_t)it.g * p.per_group + it.t) * BT;
   };
-  // token row of block tb of this lane, clamped so that every load is in
-  // bounds; a clamped row only feeds its own (discarded) output column
-  auto row_of = [&](int64_t t0, int tb) __attribute__((always_inline)) -> int64_t {
-    const int64_t t = t0 + 16 * (TB * wave + tb) + row;
+  auto issue = [&](const Pos& q, int sx, int sw) __attribute__((always_inline)) {
+    const int64_t t0 = t0_of(q.it);
+    const int64_t rows = T - t0 < BT ? T - t0 : BT;
+    const int at = q.it.ll * k + q.i;
+    const int sl = (int)((idx4[at >> 2] >> (8 * (at & 3))) & 0xff);
+    const i32x4_t rx = make_rsrc(
+        static_cast<const char*>(a.src) + ((((int64_t)sl * 2 + q.it.kv) * a.H + q.it.h) * T + t0) * G::ROWB,
+        (uint32_t)rows * G::ROWB);
+    const i32x4_t rw = make_rsrc(
+        static_cast<const char*>(q.it.kv ? a.wv : a.wk) +
+            (((int64_t)(a.l0 + q.it.ll) * a.H + q.it.h) * k + q.i) * (int64_t)(D * G::ROWB),
+        D * G::ROWB);
+#pragma unroll
+    for (int g = 0; g < G::WD; ++g)
+      dma16z(wl + (uint32_t)(sw * G::WB + (8 * g + wave) * 1024), vw[g] + (uint32_t)(q.x * 32 * G::ROWB), rw);
+#pragma unroll
+    for (int g = 0; g < G::XD; ++g)
+      dma16z(xl + (uint32_t)(sx * 8 * G::XB + g * 1024), vx[g] + (uint32_t)(q.x * 64), rx);
+  };
+  // past the end the last position repeats, so that the wait counts hold
+  auto advance = [&](Pos& q) __attribute__((always_inline)) {
+    if (q.x + 1 < G::PPS) {
+      ++q.x;
+    } else if (q.i + 1 < k) {
+      q.x = 0;
+      ++q.i;
+    } else if (q.n + cus < end) {
+      q.x = q.i = 0;
+      q.n += cus;
+      item_add(a, p, q.it, cus);
+    }
+  };
+  auto row_of = [&](int64_t t0, int r) __attribute__((always_inline)) -> int64_t {
+    const int64_t t = t0 + WT * wave + r;
     return t < T ? t : T - 1;
   };
-  auto load_x = [&](const Item& it, int i, u32x4_t (&x)[TB][S]) __attribute__((always_inline)) {
-    const uint16_t* X = x_of(it, i);
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const uint16_t* q = X + row_of(it.t0, tb) * D + 8 * c;
-#pragma unroll
-      for (int s = 0; s < S; ++s) x[tb][s] = *reinterpret_cast<const u32x4_t*>(q + 32 * s);
-    }
-  };
-  const bool stager = tid < G::PIECES;
 
   Item cur = item_of(a, p, n);
-  u32x4_t nx[TB][S];
-  uint4 wr[4];
+  Pos next = {n, cur, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    issue(next, j, j);
+    advance(next);
+  }
+
+  // lane offsets of the fragment reads
+  uint32_t fx[2];   // rows, by step of the position
+#pragma unroll
+  for (int e = 0; e < 2; ++e) fx[e] = (uint32_t)(row * 128 + 16 * ((4 * e + c) ^ ((row >> 1) & 7)));
+  uint32_t fw[NB];   // maps, by output block
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int m = 8 * c + (row >> 2);
+    fw[b] = (uint32_t)(m * G::ROWB + 32 * (b ^ map_swz<D>(m)) + 8 * (row & 3));
+  }
+
+  auto read_x = [&](int sx, u32x4_t (&x)[TB][2]) __attribute__((always_inline)) {
+    const char* xs = xp + sx * 8 * G::XB;
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) x[tb][e] = *reinterpret_cast<const u32x4_t*>(xs + tb * 2048 + fx[e]);
+  };
+  auto read_w = [&](int sw, int e, int b) __attribute__((always_inline)) -> u32x4_t {
+    const uint32_t wa = wl + (uint32_t)(sw * G::WB + e * 32 * G::ROWB) + fw[b];
+    return tr_read8(wa, wa + 4 * G::ROWB);
+  };
   float2 cs[TB][G::PL];
   int64_t cs_t0 = -1;
-  if (stager) load_piece<D>(w_of(cur, 0), tid, wr);
-  load_x(cur, 0, nx);
-  if (stager) store_piece<D, G::ROWB>(smem, tid, wr);
-  // positions one and two source layers ahead; past the end they repeat the last
-  Item i1 = cur;
-  int k1 = 0;
-  int64_t n1 = n;
-  auto advance = [&](Item& it, int& i, int64_t& m) __attribute__((always_inline)) {
-    if (i + 1 < k) {
-      ++i;
-    } else if (m + cus < end) {
-      m += cus;
-      i = 0;
-      it = item_of(a, p, m);
-    }
-  };
-  advance(i1, k1, n1);
-  if (stager) load_piece<D>(w_of(i1, k1), tid, wr);
-  __syncthreads();
 
-  int st = 0;
-  for (; n < end; n += cus) {
-    if (cur.kv == 0 && cs_t0 != cur.t0) {
+  // Position p (rows in stage sx, maps in sw).  Its rows and first map
+  // fragments are in registers when it starts.  In its middle, this wave's
+  // loads of p + 1 have landed (only those of p + 2 may be outstanding) and its
+  // reads of p - 1 are long done; with the barrier that holds for every wave:
+  // p + 1 can be read, its first reads arriving behind the second half's matrix
+  // instructions, and the loads of p + 3 go to the stages of p (rows, the wave's
+  // own) and p - 1 (maps).
+  constexpr int NPRE = D == 128 ? 2 : 4;   // more spills at D = 128
+  u32x4_t xf[TB][2], wpre[NPRE];
+  int sx = 0, sw = 0;
+  vm_wait<2 * ND>();
+  asm volatile("s_barrier" ::: "memory");
+  read_x(0, xf);
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) load_planes<D, STYLE>(a.cs_src, row_of(cur.t0, tb), c, cs[tb]);
-      cs_t0 = cur.t0;
+  for (int b = 0; b < NPRE; ++b) wpre[b] = read_w(0, 0, b);
+  for (; n < end; n += cus) {
+    const int64_t t0 = t0_of(cur);
+    if (cur.kv == 0 && cs_t0 != t0) {
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) load_planes<D, STYLE>(a.cs_src, row_of(t0, 16 * tb + row), c, cs[tb]);
+      cs_t0 = t0;
+      // a wait the compiler knows of: without it, it waits at each use, in
+      // every position, and drains the loads into LDS
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     }
     f32x4_t acc[TB][NB];
 #pragma unroll
@@ -257,206 +368,98 @@ void map_kernel(const MapArgs a, const TilePlan p) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) acc[tb][b] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
-    for (int i = 0; i < k; ++i) {
-      u32x4_t x[TB][S];
+    auto position = [&](auto xc) __attribute__((always_inline)) {
+      constexpr int X = decltype(xc)::value;
+      if (cur.kv == 0) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) strip_pos<D, STYLE, X>(xf[tb][0], xf[tb][1], cs[tb]);
+      }
+      auto mma = [&](const u32x4_t& w, int e, int b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+          acc[tb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, xf[tb][e]), acc[tb][b], 0, 0, 0);
+      };
+#pragma unroll
+      for (int b = 0; b < NB; ++b) mma(b < NPRE ? wpre[b] : read_w(sw, 0, b), 0, b);
+      u32x4_t w1[NPRE];
+#pragma unroll
+      for (int b = 0; b < NPRE; ++b) w1[b] = read_w(sw, 1, b);
+      vm_wait<ND>();
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      const int sx1 = sx + 1 == NX ? 0 : sx + 1, sw1 = (sw + 1) & (NW - 1);
+      issue(next, sx, (sw + 3) & (NW - 1));
+      advance(next);
+      u32x4_t xn[TB][2];
+      read_x(sx1, xn);
+#pragma unroll
+      for (int b = 0; b < NPRE; ++b) wpre[b] = read_w(sw1, 0, b);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) mma(b < NPRE ? w1[b] : read_w(sw, 1, b), 1, b);
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-        for (int s = 0; s < S; ++s) x[tb][s] = nx[tb][s];
-      // the next source layer's map into the stage of the previous one, then
-      // the loads after it
-      if (stager) store_piece<D, G::ROWB>(smem + (st ^ 1) * G::SLOTB, tid, wr);
-      load_x(i1, k1, nx);
-      advance(i1, k1, n1);
-      if (stager) load_piece<D>(w_of(i1, k1), tid, wr);
-      __builtin_amdgcn_sched_barrier(0);
-      if (cur.kv == 0) {
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) strip_row<D, STYLE>(x[tb], cs[tb]);
-      }
-      const char* wl = smem + st * G::SLOTB + row * G::ROWB;
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const char* ws = wl + 16 * chunk_pos<D>(4 * s + c, row);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const bf16x8_t wa = *reinterpret_cast<const bf16x8_t*>(ws + b * 16 * G::ROWB);
-#pragma unroll
-          for (int tb = 0; tb < TB; ++tb)
-            acc[tb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                wa, __builtin_bit_cast(bf16x8_t, x[tb][s]), acc[tb][b], 0, 0, 0);
-        }
-      }
-      __syncthreads();
-      st ^= 1;
+        for (int e = 0; e < 2; ++e) xf[tb][e] = xn[tb][e];
+      sx = sx1;
+      sw = sw1;
+    };
+    for (int i = 0; i < k; ++i) {
+      position(std::integral_constant<int, 0>{});
+      if constexpr (G::PPS == 2) position(std::integral_constant<int, 1>{});
     }
 
+    // The outputs go through the wave's rows of the next position, which are in
+    // registers, so that stores cover whole rows.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const int64_t lh = (int64_t)(a.l0 + cur.ll) * a.H + cur.h;
     const uint16_t* bias = reinterpret_cast<const uint16_t*>(cur.kv ? a.bv : a.bk);
     if (bias != nullptr) bias += lh * D;
-    uint16_t* out = reinterpret_cast<uint16_t*>(a.tgt) +
-                    (((int64_t)(a.l0 + cur.ll) * 2 + cur.kv) * a.H + cur.h) * a.tgt_rows * D;
+    char* out = static_cast<char*>(a.tgt) +
+                (((int64_t)(a.l0 + cur.ll) * 2 + cur.kv) * a.H + cur.h) * a.tgt_rows * G::ROWB;
+    char* os = xp + sx * 8 * G::XB;
+    constexpr int CPR = D / 8;              // 16-byte chunks of a row
+    constexpr int RPS = 64 / CPR;           // rows per store instruction
+    auto swz = [](int r) { return D == 128 ? r & 15 : (r >> 1) & 7; };
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
-      const int64_t t = row_of(cur.t0, tb);
-      const int64_t orow = SLOTS ? (int64_t)a.slots[t] : t;
-      const bool store = cur.t0 + 16 * (TB * wave + tb) + row < T &&
-                         (!SLOTS || (orow >= 0 && orow < a.tgt_rows));
-      if (cur.kv == 0) finish_row<D, STYLE, true>(acc[tb], bias, a.cs_tgt, t, c, out + orow * D, store);
-      else finish_row<D, STYLE, false>(acc[tb], bias, a.cs_tgt, t, c, out + orow * D, store);
+      const int64_t t = row_of(t0, 16 * tb + row);
+      uint2 o[NB];
+      if (cur.kv == 0) finish_row<D, STYLE, true>(acc[tb], bias, a.cs_tgt, t, c, o);
+      else finish_row<D, STYLE, false>(acc[tb], bias, a.cs_tgt, t, c, o);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        *reinterpret_cast<uint2*>(os + row * G::ROWB + 16 * ((2 * b + (c >> 1)) ^ swz(row)) + 8 * (c & 1)) = o[b];
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own writes
+#pragma unroll
+      for (int g = 0; g < 16 / RPS; ++g) {
+        const int r = RPS * g + lane / CPR, q = lane % CPR;
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(os + r * G::ROWB + 16 * q);
+        const int64_t tr = t0 + WT * wave + 16 * tb + r;
+        const int64_t orow = SLOTS ? (int64_t)a.slots[tr < T ? tr : T - 1] : tr;
+        if (tr < T && (!SLOTS || (orow >= 0 && orow < a.tgt_rows)))
+          *reinterpret_cast<u32x4_t*>(out + orow * G::ROWB + 16 * (q ^ swz(r))) = v;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // reads done before the next block's writes
     }
-    if (n + cus < end) cur = item_of(a, p, n + cus);
+    item_add(a, p, cur, cus);
   }
+  vm_wait<0>();   // no load may land in LDS after the workgroup has gone
 }
 
 template <int D, int STYLE>
-hipError_t launch_streamed(const MapArgs& a, hipStream_t stream) {
+hipError_t launch_tile(const MapArgs& a, hipStream_t stream) {
   TilePlan p;
-  p.len = BT;
   p.tiles = (int32_t)(((int64_t)a.T + BT - 1) / BT);
+  int groups = 8;
+  while (groups > 1 && a.H * (groups / 2) % 8 == 0) groups /= 2;
+  p.per_group = (p.tiles + groups - 1) / groups;
   p.items = (int64_t)a.H * 2 * p.tiles * a.nl;
   p.per_xcd = (p.items + 7) / 8;
+  const dim3 grid((unsigned)(8 * (p.per_xcd < 32 ? p.per_xcd : 32)));
   if (a.slots != nullptr)
-    hipLaunchKernelGGL((map_kernel<D, STYLE, true>), dim3(256), dim3(NTHR), 0, stream, a, p);
+    hipLaunchKernelGGL((map_kernel<D, STYLE, true>), grid, dim3(NTHR), 0, stream, a, p);
   else
-    hipLaunchKernelGGL((map_kernel<D, STYLE, false>), dim3(256), dim3(NTHR), 0, stream, a, p);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------- resident maps
-
-constexpr int RES_K = 8;       // source layers whose maps stay in LDS (head dimension 64)
-
-// One workgroup per (head, token range, K|V, target layer): the task's whole
-// map in LDS (8 KB per source layer), then the range's tiles without a barrier;
-// two workgroups a CU.  Bound by the row reads and stores: 16 -> 28 layers, 8
-// heads, k = 4, T = 8192: 0.415 ms (1.8 TB/s of the bytes it cannot do
-// without), 0.667 ms with the 64-token tiles that restaged the map per tile.
-template <int D, int STYLE, bool SLOTS>
-__global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void map_resident_kernel(const MapArgs a, const TilePlan p) {
-  using G = TileGeo<D>;
-  constexpr int S = G::S, NB = G::NB;
-  extern __shared__ __attribute__((aligned(256))) char wsm[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = lane >> 4, row = lane & 15;
-  const int64_t T = a.T;
-  const int k = a.k;
-  const int64_t n = (int64_t)(blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
-  if ((int64_t)(blockIdx.x >> 3) >= p.per_xcd || n >= p.items) return;
-  Item it = item_of(a, p, n);
-  const int64_t t_begin = it.t0;
-  const int64_t t_end = t_begin + p.len < T ? t_begin + p.len : T;
-  const int64_t lh = (int64_t)(a.l0 + it.ll) * a.H + it.h;
-
-  {
-    const uint16_t* w = reinterpret_cast<const uint16_t*>(it.kv ? a.wv : a.wk) + lh * k * (int64_t)(D * D);
-    for (int m = tid; m < k * G::PIECES; m += NTHR) {
-      const int i = m / G::PIECES, q = m % G::PIECES;
-      uint4 r[4];
-      load_piece<D>(w + i * (int64_t)(D * D), q, r);
-      store_piece<D, G::ROWB>(wsm + i * G::SLOTB, q, r);
-    }
-  }
-  const uint16_t* bias = reinterpret_cast<const uint16_t*>(it.kv ? a.bv : a.bk);
-  if (bias != nullptr) bias += lh * D;
-  uint16_t* out = reinterpret_cast<uint16_t*>(a.tgt) +
-                  (((int64_t)(a.l0 + it.ll) * 2 + it.kv) * a.H + it.h) * a.tgt_rows * D;
-  auto row_of = [&](int64_t t0, int tb) __attribute__((always_inline)) -> int64_t {
-    const int64_t t = t0 + 16 * (TB * wave + tb) + row;
-    return t < t_end ? t : t_end - 1;
-  };
-  auto load_x = [&](int i, int64_t t0, u32x4_t (&x)[TB][S]) __attribute__((always_inline)) {
-    const uint16_t* X = reinterpret_cast<const uint16_t*>(a.src) +
-                        (((int64_t)a.idx[it.ll * k + i] * 2 + it.kv) * a.H + it.h) * T * D;
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const uint16_t* q = X + row_of(t0, tb) * D + 8 * c;
-#pragma unroll
-      for (int s = 0; s < S; ++s) x[tb][s] = *reinterpret_cast<const u32x4_t*>(q + 32 * s);
-    }
-  };
-
-  u32x4_t nx[TB][S];
-  load_x(0, t_begin, nx);
-  __syncthreads();
-
-  auto sweep = [&](auto keys) __attribute__((always_inline)) {
-    constexpr bool KEYS = decltype(keys)::value;
-    for (int64_t t0 = t_begin; t0 < t_end; t0 += BT) {
-      float2 cs[TB][G::PL];
-      if (KEYS) {
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) load_planes<D, STYLE>(a.cs_src, row_of(t0, tb), c, cs[tb]);
-      }
-      f32x4_t acc[TB][NB];
-#pragma unroll
-      for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[tb][b] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-      for (int i = 0; i < k; ++i) {
-        u32x4_t x[TB][S];
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-          for (int s = 0; s < S; ++s) x[tb][s] = nx[tb][s];
-        // the next source layer's rows, or the next tile's first (the last
-        // tile loads its own again)
-        if (i + 1 < k) load_x(i + 1, t0, nx);
-        else load_x(0, t0 + BT < t_end ? t0 + BT : t0, nx);
-        __builtin_amdgcn_sched_barrier(0);
-        if (KEYS) {
-#pragma unroll
-          for (int tb = 0; tb < TB; ++tb) strip_row<D, STYLE>(x[tb], cs[tb]);
-        }
-        const char* wl = wsm + i * G::SLOTB + row * G::ROWB;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const char* ws = wl + 16 * chunk_pos<D>(4 * s + c, row);
-#pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            const bf16x8_t wa = *reinterpret_cast<const bf16x8_t*>(ws + b * 16 * G::ROWB);
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb)
-              acc[tb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  wa, __builtin_bit_cast(bf16x8_t, x[tb][s]), acc[tb][b], 0, 0, 0);
-          }
-        }
-      }
-#pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        const int64_t t = row_of(t0, tb);
-        const int64_t orow = SLOTS ? (int64_t)a.slots[t] : t;
-        const bool store = t0 + 16 * (TB * wave + tb) + row < t_end &&
-                           (!SLOTS || (orow >= 0 && orow < a.tgt_rows));
-        finish_row<D, STYLE, KEYS>(acc[tb], bias, a.cs_tgt, t, c, out + orow * D, store);
-      }
-    }
-  };
-  if (it.kv == 0) sweep(std::true_type{});
-  else sweep(std::false_type{});
-}
-
-template <int D, int STYLE>
-hipError_t launch_resident(const MapArgs& a, hipStream_t stream) {
-  // Token range of a workgroup: long enough to amortise staging the map (at
-  // 1024 tokens it is 6% of the rows read), short enough for four rounds of
-  // the 512 workgroups that fit the chip.
-  const int64_t tasks = (int64_t)a.H * 2 * a.nl;
-  int64_t len = (tasks * a.T / 2048 + BT - 1) / BT * BT;
-  len = len < BT ? BT : len > 1024 ? 1024 : len;
-  TilePlan p;
-  p.len = (int32_t)len;
-  p.tiles = (int32_t)(((int64_t)a.T + len - 1) / len);
-  p.items = tasks * p.tiles;
-  p.per_xcd = (p.items + 7) / 8;
-  if (p.per_xcd * 8 > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  const dim3 grid((unsigned)(p.per_xcd * 8));
-  const size_t lds = (size_t)a.k * TileGeo<D>::SLOTB;
-  if (a.slots != nullptr)
-    hipLaunchKernelGGL((map_resident_kernel<D, STYLE, true>), grid, dim3(NTHR), lds, stream, a, p);
-  else
-    hipLaunchKernelGGL((map_resident_kernel<D, STYLE, false>), grid, dim3(NTHR), lds, stream, a, p);
+    hipLaunchKernelGGL((map_kernel<D, STYLE, false>), grid, dim3(NTHR), 0, stream, a, p);
   return hipGetLastError();
 }
 
@@ -464,10 +467,8 @@ hipError_t launch_resident(const MapArgs& a, hipStream_t stream) {
 
 hipError_t launch_map_tile(const MapArgs& a, int d, int style, hipStream_t stream) {
   if (a.T == 0 || a.nl == 0) return hipSuccess;
-  if (d == 128) return style == 0 ? launch_streamed<128, 0>(a, stream) : launch_streamed<128, 1>(a, stream);
-  if (d == 64 && a.k <= RES_K)
-    return style == 0 ? launch_resident<64, 0>(a, stream) : launch_resident<64, 1>(a, stream);
-  if (d == 64) return style == 0 ? launch_streamed<64, 0>(a, stream) : launch_streamed<64, 1>(a, stream);
+  if (d == 128) return style == 0 ? launch_tile<128, 0>(a, stream) : launch_tile<128, 1>(a, stream);
+  if (d == 64) return style == 0 ? launch_tile<64, 0>(a, stream) : launch_tile<64, 1>(a, stream);
   return hipErrorInvalidValue;
 }
 

@@ -63,6 +63,18 @@ __device__ __forceinline__ void store_piece(char* lds, int n, const uint4 (&r)[4
 constexpr int kWStep = 8192;          // bytes of one reduction step: 32 map rows
 constexpr int kWRing = 4 * kWStep;    // staging bytes of a wave
 
+// Eight consecutive reduction indices of this lane's channel: two transposed
+// reads of four map rows each.  In each group of 16 lanes, lane i addresses 8
+// bytes (four channels) of row i / 4 and receives channel i's four rows.
+__device__ __forceinline__ u32x4_t tr_read8(uint32_t a0, uint32_t a1) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 v0 = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)a0));
+  const u32x2 v1 = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)a1));
+  return (u32x4_t){v0[0], v0[1], v1[0], v1[1]};
+}
+
 // Keep a map fragment in AGPRs from here on.
 __device__ __forceinline__ void pin_a(u32x4_t& v) { asm volatile("" : "+a"(v)); }
 
@@ -81,8 +93,6 @@ __device__ __forceinline__ void pin_a(u32x4_t& v) { asm volatile("" : "+a"(v)); 
 template <bool SPLIT, int Z0, int ZH>
 __device__ __forceinline__ void load_map_raw(u32x4_t (&wf)[8][ZH], const void* w, uint32_t map_bytes,
                                              uint32_t lds, int lane) {
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   // an opaque copy: the per-lane offsets are rebuilt here, not kept live
   asm volatile("" : "+v"(lane));
   const i32x4_t rs = make_rsrc(w, map_bytes);
@@ -118,14 +128,8 @@ __device__ __forceinline__ void load_map_raw(u32x4_t (&wf)[8][ZH], const void* w
     }
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      u32x2 v[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint32_t at = pos[b >> 1] + (uint32_t)((z & 3) * kWStep + 8 * (b & 1) + j * (SPLIT ? 4096 : 1024));
-        v[j] = __builtin_bit_cast(
-            u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at));
-      }
-      wf[b][z] = (u32x4_t){v[0][0], v[0][1], v[1][0], v[1][1]};
+      const uint32_t at = pos[b >> 1] + (uint32_t)((z & 3) * kWStep + 8 * (b & 1));
+      wf[b][z] = tr_read8(at, at + (SPLIT ? 4096 : 1024));
     }
 #pragma unroll
     for (int b = 0; b < 8; ++b) pin_a(wf[b][z]);

@@ -1,7 +1,7 @@
-"""Parity of the bf16 tile kernels with the fp64 oracle: head dimension 64 with
-the maps resident (k <= 8) and streamed (k > 8), head dimension 128 with more
-than four source layers; ragged tiles, both RoPE layouts, unequal RoPEs, dense
-and slot-addressed targets."""
+"""Parity of the bf16 tile kernel with the fp64 oracle: head dimension 64, and
+128 with more than four source layers; ragged tiles, one and several items a
+workgroup, token groups, both RoPE layouts, unequal RoPEs, dense and
+slot-addressed targets."""
 
 import numpy as np
 import pytest
@@ -19,9 +19,9 @@ CASES = {
     "d64_k1_T1": Q.replace(d=64, k=1, T=1),
     "d64_k4_T257_rebase": Q.replace(d=64, k=4, T=257, rope_src=synth.rope_dict(1e4)),
     "d64_k8_H3_T1030_interleaved": Q.replace(d=64, k=8, H=3, T=1030, rope_src=I1, rope_tgt=I1),
-    # long ranges: several tiles a workgroup and a short last range
-    "d64_k3_T2600_long_ranges": Q.replace(d=64, k=3, H=8, L_t=40, T=2600, bias="none"),
-    "d64_k9_T300_streamed": Q.replace(d=64, k=9, T=300),
+    # several items a workgroup, keys and values, a short last tile
+    "d64_k3_T2600_many_items": Q.replace(d=64, k=3, H=8, L_t=40, T=2600, bias="none"),
+    "d64_k9_T300": Q.replace(d=64, k=9, T=300),
     "d128_k5_T255": Q.replace(k=5, T=255, bias="none"),
     "d128_k8_H3_T513_rebase": Q.replace(k=8, H=3, T=513, rope_src=synth.rope_dict(1e4)),
     "d128_k6_T16_interleaved": Q.replace(k=6, T=16, rope_src=I1, rope_tgt=I1),
