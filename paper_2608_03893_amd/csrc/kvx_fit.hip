@@ -775,81 +775,90 @@ void gram_kernel(const FitArgs a, const FitPlan p) {
 
 // ------------------------------------------------------------ fit solve
 
-// The fp64 SPD solve of one fit task, blocked in 32-column panels.  The
-// p x p matrix is kept as its lower triangle in column-major order, A[j * p +
-// i] = A(i, j) for i >= j, so every panel, tile and row block below is read
-// from global memory in contiguous pieces.  A panel of p - J rows is held in
-// LDS transposed, PT[c][r] = A(J + r, J + c), so that 8 consecutive rows of
-// one column are one 64-byte read; updates run as 8 x 8 register tiles
-// (8 + 8 fp64 reads from LDS per 64 FMAs).  Copies between global memory and
-// LDS keep 8 loads per thread in flight.
-constexpr int PLD = 520;   // PT row stride (doubles): >= 512 + 8, even
+// The fp64 SPD solve of one fit task, blocked in 32-column panels, by 8 waves
+// (two per SIMD hide each other's LDS and memory latency).  The p x p matrix is
+// kept as its lower triangle in column-major order, A[j * p + i] = A(i, j) for
+// i >= j, so every panel, tile and row block below is read from global memory
+// in contiguous pieces.  A panel of p - J rows is held in LDS transposed,
+// PT[c][r] = A(J + r, J + c).  Products run on the fp64 matrix cores
+// (v_mfma_f64_16x16x4_f64, 77 TFLOP/s with one wave per SIMD): lane l supplies
+// A(l % 16, l / 16) and B(l / 16, l % 16), and element i of its result is row
+// 4 i + l / 16, column l % 16.  Copies between global memory and LDS keep 8
+// loads per thread in flight.
+// 64 target layers, 8 heads, k = 4 (1024 tasks, p = 512), ms: 10.4 with 4 waves
+// and register tiles on the vector units; now bound by the trailing updates'
+// memory traffic (11 MB a task) and the panels' serial chains.
+constexpr int SOLVE_T = 512;   // threads
+constexpr int PLD = 528;       // PT row stride (doubles): >= 512 + 1, 16 mod 32 (half a wave
+                               // reads two rows of 16 doubles on distinct banks)
+constexpr int LTS = NB + 2;    // row stride of the panel's top block by rows
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 // PT[c][r] = A(J + r, J + c) for c < 32, r < R (R <= 512)
 __device__ __forceinline__ void load_panel(const double* A, int p, int J, int R, double* PT) {
   const int t = threadIdx.x;
 #pragma unroll
   for (int c0 = 0; c0 < NB; c0 += 8) {
-    double v[8][2];
+    double v[8];
+    const int r = t < R ? t : R - 1;   // loads stay in range
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < 8; ++u) v[u] = A[(int64_t)(J + c0 + u) * p + J + r];
+    if (t < R) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int r = t + 256 * h < R ? t + 256 * h : R - 1;   // loads stay in range
-        v[u][h] = A[(int64_t)(J + c0 + u) * p + J + r];
-      }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int r = t + 256 * h;
-        if (r < R) PT[(c0 + u) * PLD + r] = v[u][h];
-      }
+      for (int u = 0; u < 8; ++u) PT[(c0 + u) * PLD + t] = v[u];
+    }
   }
 }
 
-// A(J + .., J + ..) -= L21 L21^T below the panel (lower triangle), L21 = PT rows 32 ..
+// A(J + .., J + ..) -= L21 L21^T below the panel (lower triangle), L21 = PT rows
+// 32 ..: 32 x 32 tiles, one per wave at a time.  The tile is formed transposed
+// (matrix columns along the result's rows), so that 16 lanes read and write 16
+// consecutive rows of a column.
 __device__ void syrk_update(double* A, int p, int J, const double* PT) {
-  const int R2 = p - J - NB;
-  const int n8 = (R2 + 7) / 8;
-  const int ntile = n8 * (n8 + 1) / 2;
-  for (int tile = threadIdx.x; tile < ntile; tile += 256) {
-    // u = ntile - 1 - tile enumerates the triangle row by row as (ui, uj),
-    // uj <= ui; (bi, bj) = (n8 - 1 - uj, n8 - 1 - ui) then runs down the
-    // columns, so that consecutive threads take consecutive row blocks of one
-    // column block (neighbouring addresses in the column-major matrix)
-    const int u = ntile - 1 - tile;
-    int ui = (int)((sqrtf(8.0f * (float)u + 1.0f) - 1.0f) * 0.5f);
-    while (ui * (ui + 1) / 2 > u) --ui;
-    while ((ui + 1) * (ui + 2) / 2 <= u) ++ui;
-    const int uj = u - ui * (ui + 1) / 2;
-    const int bi = n8 - 1 - uj, bj = n8 - 1 - ui;
-    // every tile lies inside the matrix (p - J - 32 is a multiple of 32); the
-    // diagonal tiles also update the unused upper triangle, which nothing
-    // reads.  The tile's old values are read first, so that their latency
-    // passes under the products.
-    double* At = A + (int64_t)(J + NB + 8 * bj) * p + J + NB + 8 * bi;
-    double acc[8][8];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int n = (p - J - NB) / 32;
+  const int ntile = n * (n + 1) / 2;
+  // tiles run down the columns of the lower triangle: (bi, bj), bi >= bj
+  int bi = wave, bj = 0;
+  for (int tile = wave; tile < ntile; tile += SOLVE_T / 64) {
+    while (bi >= n) {   // past the last row block: on to the next column
+      ++bj;
+      bi = bi - n + bj;
+    }
+    double* At = A + (int64_t)(J + NB + 32 * bj) * p + J + NB + 32 * bi;
+    // the tile's old values first: their latency passes under the products
+    f64x4_t acc[2][2];   // [column half][row half]
 #pragma unroll
-    for (int y = 0; y < 8; ++y)
+    for (int y = 0; y < 2; ++y)
 #pragma unroll
-      for (int x = 0; x < 8; ++x) acc[x][y] = At[(int64_t)y * p + x];
-    for (int c = 0; c < NB; ++c) {
-      double li[8], lj[8];
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        li[x] = PT[c * PLD + NB + 8 * bi + x];
-        lj[x] = PT[c * PLD + NB + 8 * bj + x];
+        for (int i = 0; i < 4; ++i) acc[y][x][i] = At[(int64_t)(16 * y + 4 * i + lk) * p + 16 * x + lr];
+    const double* Pj = PT + lk * PLD + NB + 32 * bj + lr;
+    const double* Pi = PT + lk * PLD + NB + 32 * bi + lr;
+#pragma unroll
+    for (int c = 0; c < NB; c += 4) {
+      double lj[2], li[2];
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        lj[y] = -Pj[c * PLD + 16 * y];
+        li[y] = Pi[c * PLD + 16 * y];
       }
 #pragma unroll
-      for (int x = 0; x < 8; ++x)
+      for (int y = 0; y < 2; ++y)
 #pragma unroll
-        for (int y = 0; y < 8; ++y) acc[x][y] = fma(-li[x], lj[y], acc[x][y]);
+        for (int x = 0; x < 2; ++x)
+          acc[y][x] = __builtin_amdgcn_mfma_f64_16x16x4f64(lj[y], li[x], acc[y][x], 0, 0, 0);
     }
+    // the diagonal tiles also write the unused upper triangle, which nothing reads
 #pragma unroll
-    for (int y = 0; y < 8; ++y)
+    for (int y = 0; y < 2; ++y)
 #pragma unroll
-      for (int x = 0; x < 8; ++x) At[(int64_t)y * p + x] = acc[x][y];
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) At[(int64_t)(16 * y + 4 * i + lk) * p + 16 * x + lr] = acc[y][x][i];
+    bi += SOLVE_T / 64;
   }
 }
 
@@ -890,13 +899,17 @@ __device__ void chol_panels(double* A, int p, double* PT) {
       if (t < NB) {
 #pragma unroll
         for (int c = 0; c < NB; ++c) PT[c * PLD + t] = row[c];   // upper part unused
-        // past the last row of column t (PLD >= 512 + 8)
-        PT[t * PLD + PLD - 1] = rdg;
+        // by rows, for the substitution below
+        double* LT = PT + NB * PLD;
+#pragma unroll
+        for (int c = 0; c < NB; ++c) LT[t * LTS + c] = row[c];
+        LT[t * LTS + NB] = rdg;
       }
     }
     __syncthreads();
     // rows 32 .. R-1: L21 = A21 L11^-T, one row per thread, in registers
-    for (int r = NB + t; r < R; r += 256) {
+    const double* LT = PT + NB * PLD;
+    if (const int r = NB + t; r < R) {
       double x[NB];
 #pragma unroll
       for (int c = 0; c < NB; ++c) x[c] = PT[c * PLD + r];
@@ -904,15 +917,15 @@ __device__ void chol_panels(double* A, int p, double* PT) {
       for (int c = 0; c < NB; ++c) {
         double v = x[c];
 #pragma unroll
-        for (int q = 0; q < c; ++q) v = fma(-x[q], PT[q * PLD + c], v);
-        x[c] = v * PT[c * PLD + PLD - 1];
+        for (int q = 0; q < c; ++q) v = fma(-x[q], LT[c * LTS + q], v);
+        x[c] = v * LT[c * LTS + NB];
       }
 #pragma unroll
       for (int c = 0; c < NB; ++c) PT[c * PLD + r] = x[c];
     }
     __syncthreads();
     for (int c = 0; c < NB; ++c)
-      for (int r = c + t; r < R; r += 256) A[(int64_t)(J + c) * p + J + r] = PT[c * PLD + r];
+      if (t >= c && t < R) A[(int64_t)(J + c) * p + J + t] = PT[c * PLD + t];
     syrk_update(A, p, J, PT);
     __syncthreads();
   }
@@ -922,76 +935,96 @@ __device__ void chol_panels(double* A, int p, double* PT) {
 // A (column-major), all 128 right-hand sides at once in blocks of 64 rows:
 //   forward   Z_i = L_ii^-1 (B_i - sum_{j < i} L_ij Z_j),
 //   backward  W_i = L_ii^-T (Z_i - sum_{j > i} L_ji^T W_j).
-// A block's right-hand sides stay in registers (thread (tr, tc): rows 8 tr ..
-// 8 tr + 7, columns tc + 32 y) while the factor's row block and the solved
-// rows stream through LDS in double-buffered chunks of 16; the block is then
-// multiplied by the inverse of its 64 x 64 diagonal block of L (or its
-// transpose), the eight inverses formed once for both sweeps.  The
-// right-hand sides are read and written once per block instead of after
-// every panel.
+// A block's right-hand sides stay in registers (wave w: rows 32 (w % 2) .. + 31,
+// columns 32 (w / 2) .. + 31, four matrix-core tiles) while the factor's row
+// block and the solved rows stream through LDS in double-buffered chunks of 16;
+// the block is then multiplied by the inverse of its 64 x 64 diagonal block of L
+// (or its transpose), the eight inverses formed once for both sweeps.  The
+// right-hand sides are read and written once per block instead of after every
+// panel.
+// LDS rows hold the reduction index, with runs of 16 columns exchanged on odd
+// rows, so that the two rows that half a wave reads fall on distinct banks.
 constexpr int SQ = 64;           // rows per block
 constexpr int SK = 16;           // reduction chunk
-constexpr int SBS = D + 1;       // row stride of the staged block (doubles)
-constexpr int SLD = SQ + 1;      // row stride of the staged diagonal block
 // LDS: chunk buffers [2][SK][SQ] of the factor and [2][SK][D] of solved rows,
-// the staged block [SQ][SBS] and diagonal block [SQ][SLD]
+// the staged block [SQ][D] and diagonal block [SQ][SQ]
 constexpr int S_LC = 0, S_ZC = S_LC + 2 * SK * SQ, S_BS = S_ZC + 2 * SK * D,
-              S_LD = S_BS + SQ * SBS, S_END = S_LD + SQ * SLD;
+              S_LD = S_BS + SQ * D, S_END = S_LD + SQ * SQ;
+__device__ __forceinline__ int swap16(int row, int col) { return col ^ (16 * (row & 1)); }
 
 template <bool BWD>
 __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
-  const int t = threadIdx.x;
-  const int tr = t >> 5, tc = t & 31;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int wr = 32 * (wave & 1), wc = 32 * (wave >> 1);
   const int nb = p / SQ;
   double* Lc = sm + S_LC;
   double* Zc = sm + S_ZC;
   double* Bs = sm + S_BS;
   double* Ld = sm + S_LD;
+  // acc += X Y over 4-row steps of LDS operands X [k][SQ], Y [k][D]
+  auto step = [&](f64x4_t (&acc)[2][2], const double* X, const double* Y, int k0) __attribute__((always_inline)) {
+    const int k = k0 + lk;
+    double xa[2], yb[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      xa[h] = X[k * SQ + swap16(k, wr + 16 * h + lr)];
+      yb[h] = Y[k * D + swap16(k, wc + 16 * h + lr)];
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[x], yb[y], acc[x][y], 0, 0, 0);
+  };
   for (int n = 0; n < nb; ++n) {
     const int i = BWD ? nb - 1 - n : n;
     const int r0 = SQ * i;
     // the block's right-hand sides
-    double acc[8][4];
+    f64x4_t acc[2][2];
 #pragma unroll
-    for (int x = 0; x < 8; ++x)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 4; ++y) acc[x][y] = B[(int64_t)(r0 + 8 * tr + x) * D + tc + 32 * y];
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[x][y][e] = B[(int64_t)(r0 + wr + 16 * x + 4 * e + lk) * D + wc + 16 * y + lr];
     // solved rows that enter: forward rows 0 .. r0 - 1, backward r0 + 64 .. p - 1
     const int k0 = BWD ? r0 + SQ : 0;
     const int nch = (BWD ? p - r0 - SQ : r0) / SK;
-    double pl[4], pz[8];
-    // chunk c: Lc[k][r] = L(r0 + r, k0 + 16 c + k) (forward) or
-    // L(k0 + 16 c + k, r0 + r) (backward); Zc[k][col] = B row k0 + 16 c + k
+    double pl[2], pz[4];
+    // chunk c: Lc[k][r] = -L(r0 + r, k0 + 16 c + k) (forward) or
+    // -L(k0 + 16 c + k, r0 + r) (backward); Zc[k][col] = B row k0 + 16 c + k
     auto fetch = [&](int c) __attribute__((always_inline)) {
       const int kb = k0 + SK * c;
       if (BWD) {
-        const int r = t >> 2, k = 4 * (t & 3);   // column r0 + r of A holds L(kb + k .., r0 + r)
+        const int r = t >> 3, k = 2 * (t & 7);   // column r0 + r of A holds L(kb + k .., r0 + r)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) pl[u] = A[(int64_t)(r0 + r) * p + kb + k + u];
+        for (int u = 0; u < 2; ++u) pl[u] = A[(int64_t)(r0 + r) * p + kb + k + u];
       } else {
-        const int k = t >> 4, r = 4 * (t & 15);  // column kb + k of A holds L(r0 + r .., kb + k)
+        const int k = t >> 5, r = 2 * (t & 31);  // column kb + k of A holds L(r0 + r .., kb + k)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) pl[u] = A[(int64_t)(kb + k) * p + r0 + r + u];
+        for (int u = 0; u < 2; ++u) pl[u] = A[(int64_t)(kb + k) * p + r0 + r + u];
       }
-      const int k = t >> 4, col = 8 * (t & 15);
+      const int k = t >> 5, col = 4 * (t & 31);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) pz[u] = B[(int64_t)(kb + k) * D + col + u];
+      for (int u = 0; u < 4; ++u) pz[u] = B[(int64_t)(kb + k) * D + col + u];
     };
     auto stash = [&](int buf) __attribute__((always_inline)) {
       double* lc = Lc + buf * SK * SQ;
       double* zc = Zc + buf * SK * D;
       if (BWD) {
-        const int r = t >> 2, k = 4 * (t & 3);
+        const int r = t >> 3, k = 2 * (t & 7);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) lc[(k + u) * SQ + r] = pl[u];
+        for (int u = 0; u < 2; ++u) lc[(k + u) * SQ + swap16(k + u, r)] = -pl[u];
       } else {
-        const int k = t >> 4, r = 4 * (t & 15);
+        const int k = t >> 5, r = 2 * (t & 31);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) lc[k * SQ + r + u] = pl[u];
+        for (int u = 0; u < 2; ++u) lc[k * SQ + swap16(k, r) + u] = -pl[u];
       }
-      const int k = t >> 4, col = 8 * (t & 15);
+      const int k = t >> 5, col = 4 * (t & 31);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) zc[k * D + col + u] = pz[u];
+      for (int u = 0; u < 4; ++u) zc[k * D + swap16(k, col) + u] = pz[u];
     };
     if (nch > 0) {
       fetch(0);
@@ -1000,20 +1033,8 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
     __syncthreads();
     for (int c = 0; c < nch; ++c) {
       if (c + 1 < nch) fetch(c + 1);
-      const double* lc = Lc + (c & 1) * SK * SQ;
-      const double* zc = Zc + (c & 1) * SK * D;
-#pragma unroll 4
-      for (int k = 0; k < SK; ++k) {
-        double l[8], z[4];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) l[x] = lc[k * SQ + 8 * tr + x];
-#pragma unroll
-        for (int y = 0; y < 4; ++y) z[y] = zc[k * D + tc + 32 * y];
-#pragma unroll
-        for (int x = 0; x < 8; ++x)
-#pragma unroll
-          for (int y = 0; y < 4; ++y) acc[x][y] = fma(-l[x], z[y], acc[x][y]);
-      }
+      for (int k = 0; k < SK; k += 4) step(acc, Lc + (c & 1) * SK * SQ, Zc + (c & 1) * SK * D, k);
       if (c + 1 < nch) stash((c + 1) & 1);
       __syncthreads();
     }
@@ -1022,43 +1043,41 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
     // stored transposed in the block's upper triangle, with the diagonal
     // 1 / L(r, r)
 #pragma unroll
-    for (int x = 0; x < 8; ++x)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 4; ++y) Bs[(8 * tr + x) * SBS + tc + 32 * y] = acc[x][y];
-    for (int e = t; e < SQ * SQ; e += 256) {
-      const int c = e >> 6, r = e & 63;   // Ld[r][c] = G(r, c): the factor applied to row c of Bs
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = wr + 16 * x + 4 * e + lk;
+          Bs[r * D + swap16(r, wc + 16 * y + lr)] = acc[x][y][e];
+        }
+    for (int e = t; e < SQ * SQ; e += SOLVE_T) {
+      const int c = e >> 6, r = e & 63;   // Ld[c][r] = G(r, c): the factor applied to row c of Bs
       double v = 0.0;
       if (r == c) v = 1.0 / A[(int64_t)(r0 + r) * p + r0 + r];
       else if (!BWD && r > c) v = A[(int64_t)(r0 + r) * p + r0 + c];   // M(r, c)
       else if (BWD && r < c) v = A[(int64_t)(r0 + c) * p + r0 + r];    // M(c, r)
-      Ld[r * SLD + c] = v;
+      Ld[c * SQ + swap16(c, r)] = v;
     }
     __syncthreads();
-    // rows 8 tr .. 8 tr + 7 of G Bs; G is lower (forward) or upper (backward)
-    // triangular, so the sum runs over k <= 8 tr + 7 or k >= 8 tr
+    // G Bs; G is lower (forward) or upper (backward) triangular, so a wave's 32
+    // rows take k < wr + 32 or k >= wr
     {
-      double out[8][4];
 #pragma unroll
-      for (int x = 0; x < 8; ++x)
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int y = 0; y < 4; ++y) out[x][y] = 0.0;
-      const int ka = BWD ? 8 * tr : 0, kz = BWD ? SQ : 8 * tr + 8;
-#pragma unroll 4
-      for (int k = ka; k < kz; ++k) {
-        double g[8], z[4];
+        for (int y = 0; y < 2; ++y) acc[x][y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+      const int ka = BWD ? wr : 0, kz = BWD ? SQ : wr + 32;
+      for (int k = ka; k < kz; k += 16)
 #pragma unroll
-        for (int x = 0; x < 8; ++x) g[x] = Ld[(8 * tr + x) * SLD + k];
+        for (int u = 0; u < 16; u += 4) step(acc, Ld, Bs, k + u);
 #pragma unroll
-        for (int y = 0; y < 4; ++y) z[y] = Bs[k * SBS + tc + 32 * y];
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int x = 0; x < 8; ++x)
+        for (int y = 0; y < 2; ++y)
 #pragma unroll
-          for (int y = 0; y < 4; ++y) out[x][y] = fma(g[x], z[y], out[x][y]);
-      }
-#pragma unroll
-      for (int x = 0; x < 8; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) B[(int64_t)(r0 + 8 * tr + x) * D + tc + 32 * y] = out[x][y];
+          for (int e = 0; e < 4; ++e)
+            B[(int64_t)(r0 + wr + 16 * x + 4 * e + lk) * D + wc + 16 * y + lr] = acc[x][y][e];
     }
     __syncthreads();
   }
@@ -1074,7 +1093,7 @@ __device__ void invert_diag_blocks(double* A, int p, double* sm) {
   constexpr int LS = SQ + 1;   // row stride of a staged block
   for (int b0 = 0; b0 < nb; b0 += 4) {
     const int nbb = nb - b0 < 4 ? nb - b0 : 4;
-    for (int e = t; e < nbb * SQ * SQ; e += 256) {
+    for (int e = t; e < nbb * SQ * SQ; e += SOLVE_T) {
       const int bb = e / (SQ * SQ), rem = e - bb * SQ * SQ, c = rem >> 6, r = rem & 63;
       const int r0 = SQ * (b0 + bb);
       sm[bb * SQ * LS + r * LS + c] = r >= c ? A[(int64_t)(r0 + c) * p + r0 + r] : 0.0;
@@ -1093,7 +1112,7 @@ __device__ void invert_diag_blocks(double* A, int p, double* sm) {
       }
     }
     __syncthreads();
-    for (int e = t; e < nbb * SQ * SQ; e += 256) {
+    for (int e = t; e < nbb * SQ * SQ; e += SOLVE_T) {
       const int bb2 = e / (SQ * SQ), rem = e - bb2 * SQ * SQ, r = rem >> 6, c = rem & 63;   // M(c, r), c > r
       const int r0 = SQ * (b0 + bb2);
       if (c > r) A[(int64_t)(r0 + c) * p + r0 + r] = sm[bb2 * SQ * LS + r * LS + c];
@@ -1108,10 +1127,12 @@ __device__ void chol_solve(double* A, double* B, int p, double* sm) {
   solve_sweep<true>(A, B, p, sm);
 }
 
-__global__ __launch_bounds__(256) void fit_solve_kernel(const FitArgs a, const FitPlan pl) {
-  // one array for the factorization's transposed panel (133 KB) and, after
-  // it, the substitutions' buffers (145 KB)
-  __shared__ double PT[S_END > NB * PLD ? S_END : NB * PLD];
+__global__ __launch_bounds__(SOLVE_T) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void fit_solve_kernel(const FitArgs a, const FitPlan pl) {
+  // one array for the factorization's transposed panel and its top block by
+  // rows (141 KB) and, after it, the substitutions' buffers (144 KB)
+  constexpr int P_END = NB * PLD + NB * LTS;
+  __shared__ double PT[S_END > P_END ? S_END : P_END];
   const int task = blockIdx.x;
   const int k = a.k, p = k * D;
   const int l = task % a.L_t, hk = task / a.L_t, kv = hk & 1, h = hk >> 1;
@@ -1119,7 +1140,7 @@ __global__ __launch_bounds__(256) void fit_solve_kernel(const FitArgs a, const F
   __shared__ double SX[4 * D];      // channel sums of the k source planes
   const int t = threadIdx.x;
   if (t < kEnt) st[t] = pl.stab[(int64_t)l * kEnt + t];
-  for (int e = t; e < p; e += 256) {
+  for (int e = t; e < p; e += SOLVE_T) {
     const int ai = e / D;
     SX[e] = a.sums[(int64_t)(((int)a.idx[l * k + ai] * 2 + kv) * a.H + h) * D + e % D];
   }
@@ -1134,27 +1155,27 @@ __global__ __launch_bounds__(256) void fit_solve_kernel(const FitArgs a, const F
   // centred design Gram + lambda I: A(i, j), i >= j, at A[j * p + i]; the
   // block of list positions (jr / D, i / D) holds it at row jr % D, column
   // i % D (at row i % D, column jr % D when the plan stores its transpose).
-  // A pass takes 16 columns jr = jb + 2 u + t / 128 (u < 8) and, per 128-row
+  // A pass takes 32 columns jr = jb + 4 u + t / 128 (u < 8) and, per 128-row
   // block q of i, row i = 128 q + t % 128; blocks above the diagonal are
   // skipped.
   {
     const int c_ = t & 127, jh = t >> 7;
 #pragma unroll 1
-    for (int jb = 0; jb < p; jb += 16)
+    for (int jb = 0; jb < p; jb += 32)
 #pragma unroll 1
       for (int q = jb >> 7; q < k; ++q) {
         const int i = 128 * q + c_;
         float g[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const int jr = jb + 2 * u + jh, r = jr & 127;
+          const int jr = jb + 4 * u + jh, r = jr & 127;
           const uint32_t v = st[(jr >> 7) * 5 + q];
           const int64_t off = (v & kTransposed) ? c_ * D + r : r * D + c_;
           g[u] = G[(int64_t)(v & ~kTransposed) * D * D + off];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const int jr = jb + 2 * u + jh;
+          const int jr = jb + 4 * u + jh;
           if (i >= jr)
             A[(int64_t)jr * p + i] = (double)g[u] - SX[i] * SX[jr] / N + (i == jr ? a.lam : 0.0);
         }
@@ -1162,16 +1183,16 @@ __global__ __launch_bounds__(256) void fit_solve_kernel(const FitArgs a, const F
   }
   // centred cross Gram B [p][128]: the cross block of list position i / D
   // holds row i % D, column c
-  for (int e0 = t; e0 < p * D; e0 += 256 * 8) {
+  for (int e0 = t; e0 < p * D; e0 += SOLVE_T * 8) {
     float g[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int e = e0 + 256 * u, i = e / D, c = e % D;
+      const int e = e0 + SOLVE_T * u, i = e / D, c = e % D;
       g[u] = G[(int64_t)st[(i / D) * 5 + 4] * D * D + (i % D) * D + c];
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int e = e0 + 256 * u, i = e / D, c = e % D;
+      const int e = e0 + SOLVE_T * u, i = e / D, c = e % D;
       B[e] = (double)g[u] - SX[i] * T[c] / N;
     }
   }
@@ -1180,7 +1201,7 @@ __global__ __launch_bounds__(256) void fit_solve_kernel(const FitArgs a, const F
   chol_solve(A, B, p, PT);
   // outputs: W rows = input features; b = mean(Y) - mean(X) W
   float* Wo = (kv == 0 ? a.W_K : a.W_V) + ((int64_t)l * a.H + h) * p * D;
-  for (int e = t; e < p * D; e += 256) Wo[e] = (float)B[e];
+  for (int e = t; e < p * D; e += SOLVE_T) Wo[e] = (float)B[e];
   if (t < D) {
     const int c = t;
     double v = T[c] / N;
@@ -1205,7 +1226,6 @@ __global__ __launch_bounds__(256) void fit_solve_kernel(const FitArgs a, const F
 // (S, T the channel sums; X^T Y the fp32 Gram output) enters Z = M X_c^T Y_c
 // on the fp64 matrix cores, and the explained sum of squares ||Z||_F^2 over
 // the target's total sum of squares is the R2.
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int PR_ROWS = 16;   // cross-block rows per stage of the probe's ring
 constexpr int PR_NST = 3;     // stages
 
@@ -1536,7 +1556,7 @@ hipError_t launch_fit(FitArgs a, void* plan, bool prep, hipStream_t stream) {
   a.jobs_per_xcd = (a.n_jobs + 7) / 8;
   hipLaunchKernelGGL(gram_kernel, dim3(8 * a.jobs_per_xcd), dim3(256), 0, stream, a, p);
   if (a.mode == 0) {
-    hipLaunchKernelGGL(fit_solve_kernel, dim3(a.L_t * a.H * 2), dim3(256), 0, stream, a, p);
+    hipLaunchKernelGGL(fit_solve_kernel, dim3(a.L_t * a.H * 2), dim3(SOLVE_T), 0, stream, a, p);
   } else {
     hipLaunchKernelGGL(probe_kernel, dim3(2 * a.L_s * a.H * 2), dim3(256), 0, stream, a);
   }
