@@ -785,9 +785,10 @@ void gram_kernel(const FitArgs a, const FitPlan p) {
 // A(l % 16, l / 16) and B(l / 16, l % 16), and element i of its result is row
 // 4 i + l / 16, column l % 16.  Copies between global memory and LDS keep 8
 // loads per thread in flight.
-// 64 target layers, 8 heads, k = 4 (1024 tasks, p = 512), ms: 10.4 with 4 waves
-// and register tiles on the vector units; now bound by the trailing updates'
-// memory traffic (11 MB a task) and the panels' serial chains.
+// 64 target layers, 8 heads, k = 4 (1024 tasks, p = 512): 6.4 ms, 10.4 ms with 4
+// waves and register tiles on the vector units.  Of the 6.4 ms the trailing
+// updates (11 MB of memory traffic a task) take about 1.4, the panels' serial
+// chains 1.6, the substitutions 1.5, the diagonal blocks' inverses 0.6.
 constexpr int SOLVE_T = 512;   // threads
 constexpr int PLD = 528;       // PT row stride (doubles): >= 512 + 1, 16 mod 32 (half a wave
                                // reads two rows of 16 doubles on distinct banks)
@@ -937,19 +938,27 @@ __device__ void chol_panels(double* A, int p, double* PT) {
 //   backward  W_i = L_ii^-T (Z_i - sum_{j > i} L_ji^T W_j).
 // A block's right-hand sides stay in registers (wave w: rows 32 (w % 2) .. + 31,
 // columns 32 (w / 2) .. + 31, four matrix-core tiles) while the factor's row
-// block and the solved rows stream through LDS in double-buffered chunks of 16;
-// the block is then multiplied by the inverse of its 64 x 64 diagonal block of L
+// block and the solved rows stream through LDS in double-buffered chunks of 32
+// (one chunk's products cover the next one's loads; chunks of 16 with loads and
+// LDS writes across the rows: 2.3 ms, now 1.5 ms, 1024 tasks, p = 512); the block is then multiplied by the inverse of its 64 x 64 diagonal block of L
 // (or its transpose), the eight inverses formed once for both sweeps.  The
 // right-hand sides are read and written once per block instead of after every
 // panel.
-// LDS rows hold the reduction index, with runs of 16 columns exchanged on odd
-// rows, so that the two rows that half a wave reads fall on distinct banks.
+// Every global load runs along the matrix's columns and every LDS write along
+// LDS rows (at 16 bytes a lane, or 8), whichever index that is:
+//   [k][n], runs of 16 columns exchanged on odd rows, so that the two rows that
+//   half a wave reads fall on distinct banks: solved rows, the forward factor,
+//   the backward diagonal block;
+//   [n][k], rows 4 banks apart: the backward factor, the forward diagonal block.
 constexpr int SQ = 64;           // rows per block
-constexpr int SK = 16;           // reduction chunk
-// LDS: chunk buffers [2][SK][SQ] of the factor and [2][SK][D] of solved rows,
-// the staged block [SQ][D] and diagonal block [SQ][SQ]
-constexpr int S_LC = 0, S_ZC = S_LC + 2 * SK * SQ, S_BS = S_ZC + 2 * SK * D,
-              S_LD = S_BS + SQ * D, S_END = S_LD + SQ * SQ;
+constexpr int SK = 32;           // reduction chunk
+constexpr int RK = SK + 2, RQ = SQ + 2;   // row strides of the [n][k] forms
+// LDS: chunk buffers [2] of the factor and [2][SK][D] of solved rows; in their
+// place afterwards the staged diagonal block and block [SQ][D]
+constexpr int S_L1 = SQ * RK;    // a factor chunk (the larger of the two forms)
+constexpr int S_LC = 0, S_ZC = S_LC + 2 * S_L1, S_END = S_ZC + 2 * SK * D;
+constexpr int S_LD = 0, S_BS = S_LD + SQ * RQ;
+static_assert(S_BS + SQ * D <= S_END, "staged blocks");
 __device__ __forceinline__ int swap16(int row, int col) { return col ^ (16 * (row & 1)); }
 
 template <bool BWD>
@@ -958,17 +967,19 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
   const int lr = lane & 15, lk = lane >> 4;
   const int wr = 32 * (wave & 1), wc = 32 * (wave >> 1);
   const int nb = p / SQ;
-  double* Lc = sm + S_LC;
-  double* Zc = sm + S_ZC;
   double* Bs = sm + S_BS;
   double* Ld = sm + S_LD;
-  // acc += X Y over 4-row steps of LDS operands X [k][SQ], Y [k][D]
-  auto step = [&](f64x4_t (&acc)[2][2], const double* X, const double* Y, int k0) __attribute__((always_inline)) {
+  // acc += X Y over a 4-row step of LDS operands X ([n][k] with row stride XS, or
+  // [k][SQ] when XS is 0) and Y [k][D]
+  auto step = [&](auto xs, f64x4_t (&acc)[2][2], const double* X, const double* Y, int k0)
+      __attribute__((always_inline)) {
+    constexpr int XS = decltype(xs)::value;
     const int k = k0 + lk;
     double xa[2], yb[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      xa[h] = X[k * SQ + swap16(k, wr + 16 * h + lr)];
+      const int r = wr + 16 * h + lr;
+      xa[h] = X[XS ? r * XS + k : k * SQ + swap16(k, r)];
       yb[h] = Y[k * D + swap16(k, wc + 16 * h + lr)];
     }
 #pragma unroll
@@ -977,9 +988,40 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
       for (int y = 0; y < 2; ++y)
         acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[x], yb[y], acc[x][y], 0, 0, 0);
   };
+  typedef double f64x2_t __attribute__((ext_vector_type(2)));
   for (int n = 0; n < nb; ++n) {
     const int i = BWD ? nb - 1 - n : n;
     const int r0 = SQ * i;
+    // solved rows that enter: forward rows 0 .. r0 - 1, backward r0 + 64 .. p - 1
+    const int k0 = BWD ? r0 + SQ : 0;
+    const int nch = (BWD ? p - r0 - SQ : r0) / SK;
+    double pl[4];
+    f64x2_t pz[4];
+    // chunk c of the factor, negated: -L(r0 + r, k0 + 32 c + k) as [k][r]
+    // (forward) or -L(k0 + 32 c + k, r0 + r) as [r][k] (backward); rows
+    // k0 + 32 c + k of B
+    auto fetch = [&](int c) __attribute__((always_inline)) {
+      const int kb = k0 + SK * c;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        pl[u] = BWD ? A[(int64_t)(r0 + (t >> 5) + 16 * u) * p + kb + (t & 31)]
+                    : A[(int64_t)(kb + (t >> 6) + 8 * u) * p + r0 + lane];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        pz[u] = *reinterpret_cast<const f64x2_t*>(&B[(int64_t)(kb + (t >> 6) + 8 * u) * D + 2 * lane]);
+    };
+    auto stash = [&](int buf) __attribute__((always_inline)) {
+      double* lc = sm + S_LC + buf * S_L1;
+      double* zc = sm + S_ZC + buf * SK * D;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = (t >> 6) + 8 * u;
+        if (BWD) lc[((t >> 5) + 16 * u) * RK + (t & 31)] = -pl[u];
+        else lc[k * SQ + swap16(k, lane)] = -pl[u];
+        *reinterpret_cast<f64x2_t*>(&zc[k * D + swap16(k, 2 * lane)]) = pz[u];
+      }
+    };
+    if (nch > 0) fetch(0);
     // the block's right-hand sides
     f64x4_t acc[2][2];
 #pragma unroll
@@ -989,59 +1031,25 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           acc[x][y][e] = B[(int64_t)(r0 + wr + 16 * x + 4 * e + lk) * D + wc + 16 * y + lr];
-    // solved rows that enter: forward rows 0 .. r0 - 1, backward r0 + 64 .. p - 1
-    const int k0 = BWD ? r0 + SQ : 0;
-    const int nch = (BWD ? p - r0 - SQ : r0) / SK;
-    double pl[2], pz[4];
-    // chunk c: Lc[k][r] = -L(r0 + r, k0 + 16 c + k) (forward) or
-    // -L(k0 + 16 c + k, r0 + r) (backward); Zc[k][col] = B row k0 + 16 c + k
-    auto fetch = [&](int c) __attribute__((always_inline)) {
-      const int kb = k0 + SK * c;
-      if (BWD) {
-        const int r = t >> 3, k = 2 * (t & 7);   // column r0 + r of A holds L(kb + k .., r0 + r)
+    // G, the inverse M = L_ii^-1 (forward) or its transpose (backward): column
+    // c = (t / 64) + 8 u of the block's upper triangle, its diagonal L(c, c);
+    // it holds M(c, q), q < c
+    double dv[8];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) pl[u] = A[(int64_t)(r0 + r) * p + kb + k + u];
-      } else {
-        const int k = t >> 5, r = 2 * (t & 31);  // column kb + k of A holds L(r0 + r .., kb + k)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) pl[u] = A[(int64_t)(kb + k) * p + r0 + r + u];
-      }
-      const int k = t >> 5, col = 4 * (t & 31);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) pz[u] = B[(int64_t)(kb + k) * D + col + u];
-    };
-    auto stash = [&](int buf) __attribute__((always_inline)) {
-      double* lc = Lc + buf * SK * SQ;
-      double* zc = Zc + buf * SK * D;
-      if (BWD) {
-        const int r = t >> 3, k = 2 * (t & 7);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) lc[(k + u) * SQ + swap16(k + u, r)] = -pl[u];
-      } else {
-        const int k = t >> 5, r = 2 * (t & 31);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) lc[k * SQ + swap16(k, r) + u] = -pl[u];
-      }
-      const int k = t >> 5, col = 4 * (t & 31);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) zc[k * D + swap16(k, col) + u] = pz[u];
-    };
-    if (nch > 0) {
-      fetch(0);
-      stash(0);
-    }
+    for (int u = 0; u < 8; ++u) dv[u] = A[(int64_t)(r0 + (t >> 6) + 8 * u) * p + r0 + lane];
+    if (nch > 0) stash(0);
     __syncthreads();
     for (int c = 0; c < nch; ++c) {
       if (c + 1 < nch) fetch(c + 1);
+      const double* lc = sm + S_LC + (c & 1) * S_L1;
+      const double* zc = sm + S_ZC + (c & 1) * SK * D;
 #pragma unroll
-      for (int k = 0; k < SK; k += 4) step(acc, Lc + (c & 1) * SK * SQ, Zc + (c & 1) * SK * D, k);
+      for (int k = 0; k < SK; k += 4) step(std::integral_constant<int, BWD ? RK : 0>{}, acc, lc, zc, k);
       if (c + 1 < nch) stash((c + 1) & 1);
       __syncthreads();
     }
-    // the diagonal block: the updated right-hand sides go to LDS, and the
-    // block's inverse M = L_ii^-1 (forward) or its transpose (backward),
-    // stored transposed in the block's upper triangle, with the diagonal
-    // 1 / L(r, r)
+    // the updated right-hand sides and the diagonal block to LDS: G as [r][k]
+    // (forward: G(c, q) = M(c, q)) or [k][r] (backward: G(q, c) = M(c, q))
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -1051,13 +1059,12 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
           const int r = wr + 16 * x + 4 * e + lk;
           Bs[r * D + swap16(r, wc + 16 * y + lr)] = acc[x][y][e];
         }
-    for (int e = t; e < SQ * SQ; e += SOLVE_T) {
-      const int c = e >> 6, r = e & 63;   // Ld[c][r] = G(r, c): the factor applied to row c of Bs
-      double v = 0.0;
-      if (r == c) v = 1.0 / A[(int64_t)(r0 + r) * p + r0 + r];
-      else if (!BWD && r > c) v = A[(int64_t)(r0 + r) * p + r0 + c];   // M(r, c)
-      else if (BWD && r < c) v = A[(int64_t)(r0 + c) * p + r0 + r];    // M(c, r)
-      Ld[c * SQ + swap16(c, r)] = v;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int c = (t >> 6) + 8 * u;
+      double v = lane < c ? dv[u] : 0.0;
+      if (lane == c) v = 1.0 / dv[u];
+      Ld[BWD ? c * SQ + swap16(c, lane) : c * RQ + lane] = v;
     }
     __syncthreads();
     // G Bs; G is lower (forward) or upper (backward) triangular, so a wave's 32
@@ -1070,7 +1077,7 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
       const int ka = BWD ? wr : 0, kz = BWD ? SQ : wr + 32;
       for (int k = ka; k < kz; k += 16)
 #pragma unroll
-        for (int u = 0; u < 16; u += 4) step(acc, Ld, Bs, k + u);
+        for (int u = 0; u < 16; u += 4) step(std::integral_constant<int, BWD ? 0 : RQ>{}, acc, Ld, Bs, k + u);
 #pragma unroll
       for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -1083,39 +1090,62 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
   }
 }
 
-// The inverses M_b = L_bb^-1 of the 64 x 64 diagonal blocks of the factor,
-// four blocks at a time in LDS, one column per thread (forward
-// substitution); M_b(r, c), r > c, is stored at A[(r0 + r) p + r0 + c] (the
-// block's unused upper triangle), its diagonal is 1 / L(r, r).
+// The inverses M_b = L_bb^-1 of the 64 x 64 diagonal blocks of the factor, four
+// blocks at a time: wave b solves L_bb x = e_j in lane j, x in registers, the
+// factor's columns read from LDS by all lanes at once.  M_b(r, c), r > c, is
+// stored at A[(r0 + r) p + r0 + c] (the block's unused upper triangle), its
+// diagonal is 1 / L(r, r).  With the column in LDS too, every term waited for
+// its own reads: 0.9 ms of the 7.3 ms solve (1024 tasks, p = 512).
 __device__ void invert_diag_blocks(double* A, int p, double* sm) {
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int nb = p / SQ;
-  constexpr int LS = SQ + 1;   // row stride of a staged block
+  constexpr int LS = SQ + 2;         // column stride of a staged block
+  constexpr int BL = SQ * LS;        // a staged block [c][r] = L(r, c), r > c; 1 / L(c, c) at r = c
   for (int b0 = 0; b0 < nb; b0 += 4) {
     const int nbb = nb - b0 < 4 ? nb - b0 : 4;
-    for (int e = t; e < nbb * SQ * SQ; e += SOLVE_T) {
-      const int bb = e / (SQ * SQ), rem = e - bb * SQ * SQ, c = rem >> 6, r = rem & 63;
-      const int r0 = SQ * (b0 + bb);
-      sm[bb * SQ * LS + r * LS + c] = r >= c ? A[(int64_t)(r0 + c) * p + r0 + r] : 0.0;
+    for (int bb = 0; bb < nbb; bb += 2) {   // an even number of blocks: p is a multiple of 128
+      double v[2][8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int r0 = SQ * (b0 + bb + h);
+          v[h][u] = A[(int64_t)(r0 + wave + 8 * u) * p + r0 + lane];
+        }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int c = wave + 8 * u;
+          double w = v[h][u];
+          if (lane == c) w = 1.0 / w;
+          if (lane >= c) sm[(bb + h) * BL + c * LS + lane] = w;
+        }
     }
     __syncthreads();
-    // thread (bb, j): column j of block bb; M(i, j) for i > j goes to the
-    // staged block's upper triangle at [j][i]
-    const int bb = t >> 6, j = t & 63;
-    if (bb < nbb) {
-      double* L = sm + bb * SQ * LS;
-      const double mjj = 1.0 / L[j * LS + j];
-      for (int i = j + 1; i < SQ; ++i) {
-        double v = L[i * LS + j] * mjj;
-        for (int q = j + 1; q < i; ++q) v = fma(L[i * LS + q], L[j * LS + q], v);
-        L[j * LS + i] = -v / L[i * LS + i];
-      }
-    }
-    __syncthreads();
-    for (int e = t; e < nbb * SQ * SQ; e += SOLVE_T) {
-      const int bb2 = e / (SQ * SQ), rem = e - bb2 * SQ * SQ, r = rem >> 6, c = rem & 63;   // M(c, r), c > r
-      const int r0 = SQ * (b0 + bb2);
-      if (c > r) A[(int64_t)(r0 + c) * p + r0 + r] = sm[bb2 * SQ * LS + r * LS + c];
+    if (wave < nbb) {
+      const double* L = sm + wave * BL;
+      double* out = A + (int64_t)SQ * (b0 + wave) * (p + 1);
+      double x[SQ];
+#pragma unroll
+      for (int i = 0; i < SQ; ++i) x[i] = i == lane ? 1.0 : 0.0;
+      static_for<0, SQ>([&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        x[q] *= L[q * LS + q];
+        if (lane < q) out[(int64_t)q * p + lane] = x[q];
+        static_for<(q + 1) / 16, SQ / 16>([&](auto gc) __attribute__((always_inline)) {
+          constexpr int i0 = 16 * decltype(gc)::value;
+#pragma unroll
+          for (int i = i0; i < i0 + 16; ++i)
+            if (i > q) {
+              x[i] = fma(-L[q * LS + i], x[q], x[i]);
+              // the term is added here and now: sunk to x[i]'s use, its reads
+              // would all wait in registers
+              asm volatile("" : "+v"(x[i]));
+            }
+          asm volatile("" ::: "memory");
+        });
+      });
     }
     __syncthreads();
   }
@@ -1130,9 +1160,11 @@ __device__ void chol_solve(double* A, double* B, int p, double* sm) {
 __global__ __launch_bounds__(SOLVE_T) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fit_solve_kernel(const FitArgs a, const FitPlan pl) {
   // one array for the factorization's transposed panel and its top block by
-  // rows (141 KB) and, after it, the substitutions' buffers (144 KB)
+  // rows (141 KB) and, after it, the diagonal blocks (132 KB) and the
+  // substitutions' buffers (96 KB)
   constexpr int P_END = NB * PLD + NB * LTS;
-  __shared__ double PT[S_END > P_END ? S_END : P_END];
+  static_assert(P_END >= S_END && P_END >= 4 * SQ * (SQ + 2), "LDS");
+  __shared__ double PT[P_END];
   const int task = blockIdx.x;
   const int k = a.k, p = k * D;
   const int l = task % a.L_t, hk = task / a.L_t, kv = hk & 1, h = hk >> 1;
