@@ -21,6 +21,7 @@
 namespace kvx {
 namespace {
 
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------- RoPE table
@@ -105,17 +106,28 @@ template <int D>
 struct Tile {
   static constexpr int BM = 64;                         // tokens per tile
   static constexpr int HALF = D / 2;
-  static constexpr int XS = D + 4;                      // LDS row stride (elements)
+  static constexpr int XS = D + 4;                      // LDS row stride of the operand tile (floats)
   static constexpr int CS = D + 4;                      // fp32 result stride
   static constexpr int X_BYTES = BM * XS * 4;
-  static constexpr int W_BYTES = D * XS * 4;
+  static constexpr int W_BYTES = D * D * 4;
   static constexpr int C_BYTES = BM * CS * 4;
   static constexpr int LDS = (X_BYTES + W_BYTES) > C_BYTES ? (X_BYTES + W_BYTES) : C_BYTES;
   static constexpr int MB = BM / 32;                    // 32-row blocks
   static constexpr int NBW = (D / 32) * MB / 4;         // 32-col blocks per wave
   static constexpr int NB_STRIDE = 4 / MB;              // wave's blocks: nb0 + q*NB_STRIDE
+  static constexpr int XP = BM * D / 8 / 256;           // 8-float pieces of the tile per thread
+  static constexpr int WP = D * D / 4 / 256;            // 4-float pieces of the map per thread
 };
 
+// Reduction order within 8 indices: step j takes index j in lanes 0..31 and
+// 4 + j in lanes 32..63, so that a lane reads its four steps of an operand row
+// as 16 bytes.  The map stays as given, [reduction][output], its 32-column runs
+// exchanged on the rows of lanes 32..63: both halves of a wave read distinct banks.
+// The next source layer's rows and map are in flight, in registers, while the
+// current one is multiplied.  Bound by the fp32 matrix rate and the two barriers
+// per source layer: 40 -> 64 layers, 8 heads, d = 128, k = 4, T = 2048: 3.26 ms (84
+// of 152 TFLOP/s; 5.93 ms with the map transposed by scalar LDS writes and no
+// loads ahead).
 template <int D, int STYLE, bool SLOTS>
 __global__ __launch_bounds__(256) void map_kernel(const MapArgs a) {
   using G = Tile<D>;
@@ -148,85 +160,91 @@ __global__ __launch_bounds__(256) void map_kernel(const MapArgs a) {
   const float* W = reinterpret_cast<const float*>(kv ? a.wv : a.wk) +
                 ((int64_t)l * a.H + h) * (int64_t)k * D * D;
 
-  for (int i = 0; i < k; ++i) {
-    const int s = a.idx[ll * k + i];
+  // Piece n of the tile for this thread: 8 channels at c0 of row r; a half-split
+  // key's pieces come in pairs, HALF apart, in one thread.
+  auto piece = [&](int n, int& r, int& c0) __attribute__((always_inline)) {
+    if (STYLE == 0) {
+      const int it = tid + 256 * (n >> 1);
+      r = it / (HALF / 8);
+      c0 = 8 * (it % (HALF / 8)) + HALF * (n & 1);
+    } else {
+      const int it = tid + 256 * n;
+      r = it / (D / 8);
+      c0 = 8 * (it % (D / 8));
+    }
+  };
+  static_assert(G::XP % 2 == 0 && G::WP >= 1, "pieces");
+  float xr[G::XP][8];
+  f32x4_t wr[G::WP];   // a native vector: arrays of float4 end up in scratch memory
+  auto load_layer = [&](int i) __attribute__((always_inline)) {
     const float* X = reinterpret_cast<const float*>(a.src) +
-                  (((int64_t)s * 2 + kv) * a.H + h) * T * D;
-    // ---- stage the operand tile: gather + inverse RoPE (keys) + round
-    if (kv == 0 && STYLE == 0) {
-      for (int it = tid; it < BM * (HALF / 8); it += 256) {
-        const int r = it / (HALF / 8), g = it % (HALF / 8);
-        const int64_t t = t0 + r;
-        float u[8], v[8];
-        if (t < T) {
-          load8(X + t * D + 8 * g, u);
-          load8(X + t * D + HALF + 8 * g, v);
+                     (((int64_t)a.idx[ll * k + i] * 2 + kv) * a.H + h) * T * D;
+#pragma unroll
+    for (int n = 0; n < G::XP; ++n) {
+      int r, c0;
+      piece(n, r, c0);
+      const int64_t t = t0 + r < T ? t0 + r : T - 1;   // a clamped row feeds only its own output row
+      load8(X + t * D + c0, xr[n]);
+    }
+#pragma unroll
+    for (int n = 0; n < G::WP; ++n)
+      wr[n] = reinterpret_cast<const f32x4_t*>(W + (int64_t)i * D * D)[tid + 256 * n];
+  };
+  load_layer(0);
+
+  for (int i = 0; i < k; ++i) {
+    if (i > 0) __syncthreads();   // the previous layer's operands are read
+    // ---- strip the source RoPE (keys) and stage the operand tile and the map
+    if (kv == 0) {
+#pragma unroll
+      for (int n = 0; n < G::XP; n += STYLE == 0 ? 2 : 1) {
+        int r, c0;
+        piece(n, r, c0);
+        const int64_t t = t0 + r < T ? t0 + r : T - 1;
+        if (STYLE == 0) {
           float c[8], sn[8];
-          load_cs8(a.cs_src + t * HALF + 8 * g, c, sn);
+          load_cs8(a.cs_src + t * HALF + c0, c, sn);
 #pragma unroll
-          for (int q = 0; q < 8; ++q) rot<true>(u[q], v[q], c[q], sn[q]);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) u[q] = v[q] = 0.0f;
-        }
-        store8(Xs + r * XS + 8 * g, u);
-        store8(Xs + r * XS + HALF + 8 * g, v);
-      }
-    } else if (kv == 0) {  // interleaved planes (2j, 2j+1)
-      for (int it = tid; it < BM * (D / 8); it += 256) {
-        const int r = it / (D / 8), g = it % (D / 8);
-        const int64_t t = t0 + r;
-        float x[8];
-        if (t < T) {
-          load8(X + t * D + 8 * g, x);
+          for (int q = 0; q < 8; ++q) rot<true>(xr[n][q], xr[n + 1][q], c[q], sn[q]);
+        } else {   // interleaved planes (2j, 2j+1)
           float c[4], sn[4];
-          load_cs4(a.cs_src + t * HALF + 4 * g, c, sn);
+          load_cs4(a.cs_src + t * HALF + c0 / 2, c, sn);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) rot<true>(x[2 * q], x[2 * q + 1], c[q], sn[q]);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) x[q] = 0.0f;
+          for (int q = 0; q < 4; ++q) rot<true>(xr[n][2 * q], xr[n][2 * q + 1], c[q], sn[q]);
         }
-        store8(Xs + r * XS + 8 * g, x);
-      }
-    } else {  // values: plain gather
-      for (int it = tid; it < BM * (D / 8); it += 256) {
-        const int r = it / (D / 8), g = it % (D / 8);
-        const int64_t t = t0 + r;
-        float x[8];
-        if (t < T) {
-          load8(X + t * D + 8 * g, x);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) x[q] = 0.0f;
-        }
-        store8(Xs + r * XS + 8 * g, x);
       }
     }
-    // ---- stage W block i transposed: Ws[n][kk] = W[i*D + kk][n]
-    for (int it = tid; it < D * (D / 8); it += 256) {
-      const int kk = it / (D / 8), ng = it % (D / 8);
-      const float* wrow = W + ((int64_t)i * D + kk) * D + 8 * ng;
-      float w8[8];
-      load8(wrow, w8);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) Ws[(8 * ng + q) * XS + kk] = w8[q];
+    for (int n = 0; n < G::XP; ++n) {
+      int r, c0;
+      piece(n, r, c0);
+      store8(Xs + r * XS + c0, xr[n]);
     }
+#pragma unroll
+    for (int n = 0; n < G::WP; ++n) {
+      const int e = 4 * (tid + 256 * n), kk = e / D, c0 = e % D;
+      *reinterpret_cast<f32x4_t*>(Ws + kk * D + (c0 ^ (32 * ((kk >> 2) & 1)))) = wr[n];
+    }
+    if (i + 1 < k) load_layer(i + 1);
     __syncthreads();
     // ---- contraction on the matrix cores
-    const int arow = mb * 32 + (lane & 31);
+    const int hi = lane >> 5, col = lane & 31;
+    const float* xrow = Xs + (mb * 32 + col) * XS + 4 * hi;
+    const float* wrow = Ws + 4 * hi * D;
 #pragma unroll 4
-    for (int ks = 0; ks < D / 2; ++ks) {
-      const int kof = ks * 2 + (lane >> 5);
-      const float av = Xs[arow * XS + kof];
+    for (int m = 0; m < D / 8; ++m) {
+      const float4 av = *reinterpret_cast<const float4*>(xrow + 8 * m);
+      const float x4[4] = {av.x, av.y, av.z, av.w};
 #pragma unroll
-      for (int q = 0; q < G::NBW; ++q) {
-        const int n = (nb0 + q * G::NB_STRIDE) * 32 + (lane & 31);
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, Ws[n * XS + kof], acc[q], 0, 0, 0);
-      }
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < G::NBW; ++q) {
+          const int n = ((nb0 + q * G::NB_STRIDE) * 32 ^ (32 * hi)) + col;
+          acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(x4[j], wrow[(8 * m + j) * D + n], acc[q], 0, 0, 0);
+        }
     }
-    __syncthreads();
   }
+  __syncthreads();
 
   // ---- accumulators to LDS (fp32), then bias + target RoPE + rounded store
 #pragma unroll

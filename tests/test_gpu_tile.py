@@ -52,6 +52,24 @@ def test_tile_parity(gpu_kvx, name):
     assert torch.equal(pool, want), name
 
 
+F32_CASES = {
+    "f32_d128_k3_T65": Q.replace(dtype="f32", k=3, T=65),
+    "f32_d128_k1_T1_interleaved": Q.replace(dtype="f32", k=1, T=1, rope_src=I1, rope_tgt=I1, bias="none"),
+    "f32_d128_k5_T130_interleaved": Q.replace(dtype="f32", k=5, H=3, T=130, rope_src=I1, rope_tgt=I1),
+    "f32_d64_k9_T64_rebase": Q.replace(dtype="f32", d=64, k=9, T=64, rope_src=synth.rope_dict(1e4)),
+    "f32_d64_k2_T300_interleaved": Q.replace(dtype="f32", d=64, k=2, T=300, rope_src=I1, rope_tgt=I1),
+}
+
+
+@pytest.mark.parametrize("name", sorted(F32_CASES))
+def test_f32_tile_parity(gpu_kvx, name):
+    """fp32: rows and maps of the next source layer in registers, reduction
+    order interleaved within 8 indices, exchanged map columns."""
+    cfg = F32_CASES[name]
+    inp = synth.make_inputs(cfg, DEV)
+    assert_parity(np32(run_gpu(gpu_kvx, inp)), oracle_rows(inp), TOL["f32"], name)
+
+
 @pytest.mark.parametrize("d,k", [(64, 2), (128, 5)])
 def test_tile_kernel_leaves_non_finite_rows_alone(gpu_kvx, d, k):
     """A token whose source row holds infinities or NaN spoils its own output row only."""
