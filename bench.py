@@ -37,10 +37,12 @@ METRIC = "mapped KV tokens/sec (all layers x heads) + % of HBM/MFMA roofline"
 # tied to their hash)
 KERNEL_SOURCES = {
     "map_ks2_kernel": ["paper_2608_03893_amd/csrc/kvx_map_ks2.hip",
+                       "paper_2608_03893_amd/csrc/kvx_wload.h",
                        "paper_2608_03893_amd/csrc/kvx_asm.h",
                        "paper_2608_03893_amd/csrc/kvx_bf16.h",
                        "paper_2608_03893_amd/csrc/kvx_internal.h"],
     "map_ks_kernel": ["paper_2608_03893_amd/csrc/kvx_map_ks.hip",
+                      "paper_2608_03893_amd/csrc/kvx_wload.h",
                       "paper_2608_03893_amd/csrc/kvx_asm.h",
                       "paper_2608_03893_amd/csrc/kvx_bf16.h",
                       "paper_2608_03893_amd/csrc/kvx_internal.h"],
@@ -48,8 +50,11 @@ KERNEL_SOURCES = {
                          "paper_2608_03893_amd/csrc/kvx_bf16.h",
                          "paper_2608_03893_amd/csrc/kvx_internal.h"],
     "map_w_kernel": ["paper_2608_03893_amd/csrc/kvx_map_bf16.hip",
+                     "paper_2608_03893_amd/csrc/kvx_wload.h",
                      "paper_2608_03893_amd/csrc/kvx_internal.h"],
     "map_kernel": ["paper_2608_03893_amd/csrc/kvx_kernels.hip",
+                   "paper_2608_03893_amd/csrc/kvx_map_tile.hip",
+                   "paper_2608_03893_amd/csrc/kvx_wload.h",
                    "paper_2608_03893_amd/csrc/kvx_internal.h"],
     "gram_kernel": ["paper_2608_03893_amd/csrc/kvx_fit.hip",
                     "paper_2608_03893_amd/csrc/kvx_bf16.h",

@@ -296,6 +296,16 @@ Kernel choose_kernel(int dt, const kvx_dims& m, int nl, int64_t tgt_rows, bool s
   // (loading the maps, filling the pipeline).
   const int segs = kvx::plan_sweep(nl, m.H, m.T).segs;
   if (m.H * segs % 8 == 0 && nl >= 16) {
+    // Short calls at k = 1 and 3: a CU's few tiles in the k-split kernel do not
+    // cover its unit starts, and the W-stationary kernel's workgroups fill the
+    // chip, but where 64 layers make 32 whole pairs of a few tiles.  Measured, 8
+    // heads, us, k-split / W-stationary: k = 3, 24 layers, 512 tokens 72 / 56;
+    // 80 layers, 1024 tokens 273 / 245; 36 layers, 4096 tokens 409 / 413; 64
+    // layers, 64 tokens 50 / 62; k = 1, 36 layers, 512 tokens 49 / 47, 1024
+    // tokens 83 / 88.
+    // (16 layers, one group of 8 pairs and 4 token parts, gain least and stay.)
+    if (nl > 16 && m.k == 3 && m.T <= 1024 && (nl < 64 || m.T >= 512)) return Kernel::W;
+    if (nl > 16 && m.k == 1 && m.T <= 512 && nl < 64) return Kernel::W;
     if (ks2_ok) return Kernel::Ks2;
     if (ks_ok) return Kernel::Ks;
     return Kernel::Sweep;

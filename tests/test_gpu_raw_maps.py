@@ -26,9 +26,11 @@ CASES = {
 
 
 @pytest.mark.parametrize("name", sorted(CASES))
-def test_packed_images_of_an_unflagged_call(gpu_kvx, name):
+def test_packed_images_of_an_unflagged_call(gpu_kvx, name, monkeypatch):
     cfg, kernel = CASES[name]
     kvx = gpu_kvx
+    if kernel == "map_ks_kernel":   # by default short calls at k = 1 and 3 take map_w_kernel
+        monkeypatch.setenv("KVX_KERNEL", "ks")
     inp = synth.make_inputs(cfg, DEV)
     dims = kvx.Dims(L_s=cfg.L_s, L_t=cfg.L_t, H=cfg.H, T=cfg.T, d=cfg.d, k=cfg.k)
     assert kvx.map_kernel_name(dims) == kernel
