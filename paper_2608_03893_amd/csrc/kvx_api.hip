@@ -266,15 +266,15 @@ kvx_status validate(const Call& c) {
   return KVX_OK;
 }
 
-// Which kernel runs a call: the general tile kernel; the W-stationary kernel
-// (bf16, d = 128, k <= 4; one workgroup per task and token range); or one of
-// the layer-sweep kernels (same cases; one workgroup per CU, all target layers
-// of a head swept together): the k-split kernel with the mid-tile barrier for
-// k = 2 and 4, the k-split kernel for k = 1 and 3.  KVX_KERNEL = tile | w |
+// Which kernel runs a call: the tile kernels (fp32; bf16 with d = 64 or k > 4);
+// the W-stationary kernel (bf16, d = 128, k <= 4; one workgroup per task and
+// token range); or one of the layer-sweep kernels (same cases; one workgroup per
+// CU, all target layers of a head swept together): the k-split kernel with the
+// mid-tile barrier for k = 2 and 4, the k-split kernel for k = 1 and 3.  KVX_KERNEL = tile | w |
 // sweep | ks | ks2 overrides the choice (tuning and tests).  The
 // W-stationary and sweep kernels give bit-identical results; the
 // k-split kernels add two partial sums per output and round in another
-// order.  All kernels read the same packed maps.
+// order.  All but the tile kernels share the packed maps.
 enum class Kernel { Tile, W, Sweep, Ks, Ks2 };
 
 Kernel choose_kernel(int dt, const kvx_dims& m, int nl, int64_t tgt_rows, bool slots,

@@ -52,8 +52,10 @@ constexpr int HALF = 64;
 // pi(rho); column kappa = 32*(4i + s) + 8c' + q holds input feature
 // 128i + sigma(s, c', q).  Each 16-byte chunk u = kappa / 8 of row rho is
 // stored at chunk position u ^ (rho & 15), so the 16 rows read by one MFMA
-// fragment load fall on distinct LDS banks.  pack_w_kernel writes this image
-// to global memory once per call; workgroups copy it to LDS as is.
+// fragment load fall on distinct LDS banks.  A workgroup transposes W into this
+// image, or copies the image of an earlier call; the first token range's
+// workgroups leave it in global memory.  pack_w_kernel writes it for the
+// layer-sweep kernel.
 __device__ __forceinline__ int out_row(int n) {   // output channel -> rho
   const int b = 2 * (n / 32) + (n % 8) / 4;
   const int c = (n % 32) / 8;
