@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void xhead_strip_kernel(const uint16_t* __rest
                                                           uint16_t* __restrict__ xs, int L_s,
                                                           int H, int T) {
   // thread = (token t, 8 planes q); it loads their (cos, sin) once and strips
-  // the row of every (layer, head) key plane, so the table is read once
+  // the row of the key planes (layer, head) of its part of the grid
   constexpr int TPR = D / 16;   // threads per row
   const int i = (int)blockIdx.x * 256 + (int)threadIdx.x;
   if (i >= T * TPR) return;     // T * d * 2 < 2^32 (checked on the host)
@@ -68,26 +68,40 @@ __global__ __launch_bounds__(256) void xhead_strip_kernel(const uint16_t* __rest
   const int o2 = STYLE == 0 ? D / 2 + 8 * q : 16 * q + 8;
   const int64_t row = (int64_t)t * D;
   const int64_t plane = (int64_t)T * D;
-  for (int s = 0; s < L_s; ++s) {
-    const uint16_t* in = src + (int64_t)s * 2 * H * plane + row;   // key planes of layer s
-    uint16_t* out = xs + (int64_t)s * H * plane + row;
-    for (int g = 0; g < H; ++g, in += plane, out += plane) {
-      float a[8], b[8];
-      unpack8(*reinterpret_cast<const uint4*>(in + o1), a);
-      unpack8(*reinterpret_cast<const uint4*>(in + o2), b);
+  const int planes = L_s * H;
+  const int per = (planes + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int p0 = (int)blockIdx.y * per;
+  const int p1 = p0 + per < planes ? p0 + per : planes;
+  for (int p = p0; p < p1; ++p) {
+    const int s = p / H, g = p - s * H;
+    const uint16_t* in = src + ((int64_t)s * 2 * H + g) * plane + row;   // key planes of layer s
+    uint16_t* out = xs + (int64_t)p * plane + row;
+    float a[8], b[8];
+    unpack8(*reinterpret_cast<const uint4*>(in + o1), a);
+    unpack8(*reinterpret_cast<const uint4*>(in + o2), b);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        // plane e: (u, v) = (a[e], b[e]) half-split; consecutive pairs interleaved
-        float& u = STYLE == 0 ? a[e] : (e < 4 ? a[2 * e] : b[2 * e - 8]);
-        float& v = STYLE == 0 ? b[e] : (e < 4 ? a[2 * e + 1] : b[2 * e - 7]);
-        const float u0 = u, v0 = v;
-        u = __builtin_fmaf(u0, w[e].x, v0 * w[e].y);    // inverse rotation: angle -a
-        v = __builtin_fmaf(v0, w[e].x, -(u0 * w[e].y));
-      }
-      *reinterpret_cast<uint4*>(out + o1) = pack8(a);
-      *reinterpret_cast<uint4*>(out + o2) = pack8(b);
+    for (int e = 0; e < 8; ++e) {
+      // plane e: (u, v) = (a[e], b[e]) half-split; consecutive pairs interleaved
+      float& u = STYLE == 0 ? a[e] : (e < 4 ? a[2 * e] : b[2 * e - 8]);
+      float& v = STYLE == 0 ? b[e] : (e < 4 ? a[2 * e + 1] : b[2 * e - 7]);
+      const float u0 = u, v0 = v;
+      u = __builtin_fmaf(u0, w[e].x, v0 * w[e].y);    // inverse rotation: angle -a
+      v = __builtin_fmaf(v0, w[e].x, -(u0 * w[e].y));
     }
+    *reinterpret_cast<uint4*>(out + o1) = pack8(a);
+    *reinterpret_cast<uint4*>(out + o2) = pack8(b);
   }
+}
+
+// The grid's planes are split until 2048 workgroups (8 per CU) are there: with
+// every plane in one thread's loop a short call is bound by the latency of its
+// loads (40 layers, 8 heads, 8192 tokens: 467 us, 2.9 TB/s; split, a cross-head
+// call on 64 target layers 8.12 -> 7.86 ms).
+inline dim3 strip_grid(int T, int d, int L_s, int H) {
+  const int64_t x = ((int64_t)T * (d / 16) + 255) / 256;
+  const int64_t y = (2048 + x - 1) / x;
+  const int64_t planes = (int64_t)L_s * H;
+  return dim3((unsigned)x, (unsigned)(y < planes ? y : planes));
 }
 
 // ---------------------------------------------------------------------------
@@ -442,7 +456,7 @@ hipError_t launch_all_d(const XArgs& a, int style, bool strip, bool pack, const 
                         const uint16_t* wv, const float2* cs_src, hipStream_t stream) {
   const int F = a.k * a.H_s * D, N = a.H_t * D;
   if (strip) {
-    const dim3 grid((unsigned)((a.T * (D / 16) + 255) / 256));
+    const dim3 grid = strip_grid(a.T, D, a.L_s, a.H_s);
     if (style == 0)
       hipLaunchKernelGGL((xhead_strip_kernel<D, 0>), grid, dim3(256), 0, stream, a.src, cs_src,
                          const_cast<uint16_t*>(a.xs), a.L_s, a.H_s, a.T);
@@ -470,13 +484,13 @@ hipError_t launch_strip_keys(const uint16_t* src, const float2* cs, uint16_t* xs
                              int T, int d, int style, hipStream_t stream) {
   if (T == 0) return hipSuccess;
   if (d == 128) {
-    const dim3 grid((unsigned)((T * (128 / 16) + 255) / 256));
+    const dim3 grid = strip_grid(T, d, L_s, H);
     if (style == 0)
       hipLaunchKernelGGL((xhead_strip_kernel<128, 0>), grid, dim3(256), 0, stream, src, cs, xs, L_s, H, T);
     else
       hipLaunchKernelGGL((xhead_strip_kernel<128, 1>), grid, dim3(256), 0, stream, src, cs, xs, L_s, H, T);
   } else if (d == 64) {
-    const dim3 grid((unsigned)((T * (64 / 16) + 255) / 256));
+    const dim3 grid = strip_grid(T, d, L_s, H);
     if (style == 0)
       hipLaunchKernelGGL((xhead_strip_kernel<64, 0>), grid, dim3(256), 0, stream, src, cs, xs, L_s, H, T);
     else
