@@ -15,8 +15,9 @@
 // 64 bytes per instruction, neighbouring lanes in different rows) run at 18
 // bytes per clock and CU even out of L2 (9.7 TB/s over the chip); with 64
 // contiguous bytes per four neighbouring lanes the same loads reach 33 TB/s.
-// Bound by the key strip and the waits around the position barrier (matrix
-// pipe busy about 30%).  Qwen3-14B->32B shapes, k = 8, T = 8191: 3.29 ms (0.67
+// Bound at k = 8 by traffic beyond L2 (14.6 GB at 4.2 TB/s: the maps are read
+// again for every 256 tokens), the key strip and the waits around the position
+// barrier (matrix pipe busy about 30%).  Qwen3-14B->32B shapes, k = 8, T = 8191: 3.29 ms (0.67
 // PFLOP/s; 4.35 ms with rows straight into registers and barriers per source
 // layer, 16.95 ms with 64-token tiles staged without a pipeline); head
 // dimension 64, 16 -> 28 layers, k = 4, T = 8192: 0.369 ms (0.415 and 0.667).
