@@ -178,7 +178,7 @@ void map_w_kernel(const MapArgs a) {
     constexpr int PER = 512 / NT;   // 4 x 8 pieces of a source layer's map per thread
     uint4 r[PER][4];
 #pragma unroll
-    for (int n = 0; n < PER; ++n) load_piece<D>(W, tid + n * NT, r[n]);
+    for (int n = 0; n < PER; ++n) load_piece(W, tid + n * NT, r[n]);
 #pragma unroll
     for (int i = 0; i < K; ++i)
 #pragma unroll
@@ -186,8 +186,8 @@ void map_w_kernel(const MapArgs a) {
         uint4 q[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) q[j] = r[n][j];
-        if (i + 1 < K) load_piece<D>(W + (i + 1) * D * D, tid + n * NT, r[n]);
-        store_piece<D, KD * 2>(reinterpret_cast<char*>(Wt) + i * 256, tid + n * NT, q);
+        if (i + 1 < K) load_piece(W + (i + 1) * D * D, tid + n * NT, r[n]);
+        store_piece<KD * 2>(reinterpret_cast<char*>(Wt) + i * 256, tid + n * NT, q);
       }
   } else {
     stage_wt<K, NT>(Wt, img, tid);

@@ -11,42 +11,29 @@ namespace {
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Wint-to-pointer-cast"   // LDS addresses; the host pass sees wider pointers
 
-// Position of 16-byte chunk q of map row rho: the 16 rows of a fragment read
-// fall on distinct LDS banks (row bytes: one or half a sweep of the 64 banks).
-template <int D>
-__device__ __forceinline__ int chunk_pos(int q, int rho) {
-  return D == 128 ? q ^ (rho & 15) : q ^ ((rho >> 1) & 7);
-}
-
 // One 4 x 8 piece of a source layer's map: input rows 4 kg .. + 3, output
 // channels 8 ng .. + 7.  The lanes of half a wave take 8 kg and 4 ng, whose
 // 8-byte LDS writes of one channel fall on distinct banks; the wave reads
 // whole 128-byte lines.
-template <int D>
 __device__ __forceinline__ void piece_of(int n, int& kg, int& ng) {
-  if (D == 128) {
-    kg = (n & 7) | ((n >> 7) << 3);
-    ng = ((n >> 3) & 3) | (((n >> 5) & 3) << 2);
-  } else {
-    kg = (n & 7) | ((n >> 6) << 3);
-    ng = ((n >> 3) & 3) | (((n >> 5) & 1) << 2);
-  }
+  kg = (n & 7) | ((n >> 7) << 3);
+  ng = ((n >> 3) & 3) | (((n >> 5) & 3) << 2);
 }
 
-template <int D>
 __device__ __forceinline__ void load_piece(const uint16_t* __restrict__ w, int n, uint4 (&r)[4]) {
   int kg, ng;
-  piece_of<D>(n, kg, ng);
+  piece_of(n, kg, ng);
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    r[j] = *reinterpret_cast<const uint4*>(w + (4 * kg + j) * D + 8 * ng);
+    r[j] = *reinterpret_cast<const uint4*>(w + (4 * kg + j) * 128 + 8 * ng);
 }
 
-// Into LDS at row stride ROWB.
-template <int D, int ROWB>
+// Into LDS at row stride ROWB, 16-byte chunk q of map row rho at position q ^
+// (rho % 16): the 16 rows of a fragment read fall on distinct banks.
+template <int ROWB>
 __device__ __forceinline__ void store_piece(char* lds, int n, const uint4 (&r)[4]) {
   int kg, ng;
-  piece_of<D>(n, kg, ng);
+  piece_of(n, kg, ng);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int rho = 16 * (2 * (ng >> 2) + (e >> 2)) + 4 * (ng & 3) + (e & 3);
@@ -56,7 +43,7 @@ __device__ __forceinline__ void store_piece(char* lds, int n, const uint4 (&r)[4
     for (int j = 0; j < 4; ++j) w[j] = (&r[j].x)[e >> 1];
     const uint2 v = make_uint2(__builtin_amdgcn_perm(w[1], w[0], sel),
                                __builtin_amdgcn_perm(w[3], w[2], sel));
-    *reinterpret_cast<uint2*>(lds + rho * ROWB + 16 * chunk_pos<D>(kg >> 1, rho) + 8 * (kg & 1)) = v;
+    *reinterpret_cast<uint2*>(lds + rho * ROWB + 16 * ((kg >> 1) ^ (rho & 15)) + 8 * (kg & 1)) = v;
   }
 }
 
