@@ -54,6 +54,7 @@
 #include "kvx_asm.h"
 #include "kvx_bf16.h"
 #include "kvx_internal.h"
+#include "kvx_pair.h"
 #include "kvx_wload.h"
 
 // This source is compiled twice: for the packed images of an earlier call, and
@@ -864,55 +865,6 @@ bool map_ks2_supported(int k, int64_t T, int64_t tgt_rows, bool slots, bool tgt_
 }
 #endif
 
-static void ks2_pair_order(const uint8_t* idx, int k, int g0, int g_n, uint8_t* order) {
-  // sh[i][j]: sources of layer j that layer i also lists (the slots of a
-  // pair's second layer that read the first layer's)
-  int sh[64][64];
-  for (int i = 0; i < g_n; ++i)
-    for (int j = 0; j < g_n; ++j) {
-      int n = 0;
-      for (int r = 0; r < k; ++r)
-        for (int t = 0; t < k; ++t)
-          if (idx[(g0 + j) * k + r] == idx[(g0 + i) * k + t]) {
-            ++n;
-            break;
-          }
-      sh[i][j] = n;
-    }
-  auto s = [&](int i, int j) { return sh[i][j] > sh[j][i] ? sh[i][j] : sh[j][i]; };
-  // Each CU keeps its pair for the whole launch, so the pairs that share
-  // nothing set the time: match as many layers as possible to a partner that
-  // shares a source.  Min-degree greedy: the unmatched layer with the fewest
-  // unmatched sharing partners takes the partner that shares the most (then
-  // the one with the fewest partners left); the rest are paired in order.
-  bool used[64] = {};
-  int deg[64];
-  for (int i = 0; i < g_n; ++i) {
-    deg[i] = 0;
-    for (int j = 0; j < g_n; ++j) deg[i] += j != i && s(i, j) > 0;
-  }
-  int n = 0;
-  for (;;) {
-    int i = -1;
-    for (int c = 0; c < g_n; ++c)
-      if (!used[c] && deg[c] > 0 && (i < 0 || deg[c] < deg[i])) i = c;
-    if (i < 0) break;
-    int j = -1;
-    for (int c = 0; c < g_n; ++c)
-      if (!used[c] && c != i && s(i, c) > 0 &&
-          (j < 0 || s(i, c) > s(i, j) || (s(i, c) == s(i, j) && deg[c] < deg[j])))
-        j = c;
-    const int a = sh[i][j] >= sh[j][i] ? i : j, b = a == i ? j : i;
-    order[g0 + n++] = (uint8_t)a;
-    order[g0 + n++] = (uint8_t)b;
-    used[i] = used[j] = true;
-    for (int c = 0; c < g_n; ++c)
-      if (!used[c]) deg[c] -= (s(c, i) > 0) + (s(c, j) > 0);
-  }
-  for (int c = 0; c < g_n; ++c)
-    if (!used[c]) order[g0 + n++] = (uint8_t)c;
-}
-
 #if KVX_RAW_MAPS
 hipError_t launch_map_ks2_raw(
 #else
@@ -926,7 +878,7 @@ hipError_t launch_map_ks2(
   int g0 = 0;
   for (int g = 0; g < sp.n_groups; ++g) {
     const int g_n = g < sp.full_groups ? 64 : sp.rest_len[g - sp.full_groups];
-    ks2_pair_order(a.idx, a.k, g0, g_n, p.order);
+    ks2_pair_order(a.idx + g0 * a.k, a.k, g_n, p.order + g0);
     g0 += g_n;
   }
   switch (a.k) {
