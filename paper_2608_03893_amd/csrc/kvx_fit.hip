@@ -874,8 +874,9 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // Cholesky of the p x p matrix A (lower triangle, column-major, fp64, global
 // memory) in place.
 __device__ void chol_panels(double* A, int p, double* PT) {
-  const int t = threadIdx.x;
   for (int J = 0; J < p; J += NB) {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));   // its masks are formed in the loop: kept over it, they spill
     const int R = p - J;
     load_panel(A, p, J, R, PT);
     __syncthreads();
@@ -1098,12 +1099,14 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
 // diagonal is 1 / L(r, r).  With the column in LDS too, every term waited for
 // its own reads: 0.9 ms of the 7.3 ms solve (1024 tasks, p = 512).
 __device__ void invert_diag_blocks(double* A, int p, double* sm) {
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int wave = threadIdx.x >> 6;
   const int nb = p / SQ;
   constexpr int LS = SQ + 2;         // column stride of a staged block
   constexpr int BL = SQ * LS;        // a staged block [c][r] = L(r, c), r > c; 1 / L(c, c) at r = c
   for (int b0 = 0; b0 < nb; b0 += 4) {
     const int nbb = nb - b0 < 4 ? nb - b0 : 4;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // its masks are formed here: kept over the loop, they spill
     for (int bb = 0; bb < nbb; bb += 2) {   // an even number of blocks: p is a multiple of 128
       double v[2][8];
 #pragma unroll
@@ -1126,14 +1129,16 @@ __device__ void invert_diag_blocks(double* A, int p, double* sm) {
     __syncthreads();
     if (wave < nbb) {
       const double* L = sm + wave * BL;
-      double* out = A + (int64_t)SQ * (b0 + wave) * (p + 1);
+      double* out = A + (int64_t)SQ * (b0 + wave) * (p + 1) + lane;
       double x[SQ];
 #pragma unroll
       for (int i = 0; i < SQ; ++i) x[i] = i == lane ? 1.0 : 0.0;
       static_for<0, SQ>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value;
         x[q] *= L[q * LS + q];
-        if (lane < q) out[(int64_t)q * p + lane] = x[q];
+        if (lane < q) *out = x[q];
+        out += p;
+        asm volatile("" : "+v"(out));
         static_for<(q + 1) / 16, SQ / 16>([&](auto gc) __attribute__((always_inline)) {
           constexpr int i0 = 16 * decltype(gc)::value;
 #pragma unroll
