@@ -345,7 +345,8 @@ void map_kernel(const MapArgs a, const TilePlan p) {
   // p + 1 can be read, its first reads arriving behind the second half's matrix
   // instructions, and the loads of p + 3 go to the stages of p (rows, the wave's
   // own) and p - 1 (maps).
-  constexpr int NPRE = D == 128 ? 2 : 4;   // more spills at D = 128
+  // map fragments read ahead: one more spills in the loop whose loads are counted
+  constexpr int NPRE = D == 64 ? 4 : STYLE == 0 ? 2 : 1;
   u32x4_t xf[TB][2], wpre[NPRE];
   int sx = 0, sw = 0;
   vm_wait<2 * ND>();
