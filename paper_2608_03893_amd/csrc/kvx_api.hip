@@ -308,7 +308,9 @@ Kernel choose_kernel(int dt, const kvx_dims& m, int nl, int64_t tgt_rows, bool s
     if (nl > 16 && m.k == 1 && m.T <= 512 && nl < 64) return Kernel::W;
     if (ks2_ok) return Kernel::Ks2;
     if (ks_ok) return Kernel::Ks;
-    return Kernel::Sweep;
+    // planes beyond the k-split kernels' 32-bit offsets (16.7 million rows); with
+    // few or odd heads the layer-sweep kernel has no measurement in its favour
+    if (m.H % 8 == 0) return Kernel::Sweep;
   }
   return Kernel::W;
 }

@@ -25,6 +25,11 @@ import pytest
     (36, 8, 513, 1, "map_ks_kernel"),
     (64, 8, 512, 1, "map_ks_kernel"),
     (64, 8, 8192, 5, "map_kernel"),
+    # planes of 4 GiB and more, whose offsets the k-split kernels cannot hold
+    (16, 8, 20_000_000, 4, "map_sweep_kernel"),
+    (16, 1, 16_000_000, 4, "map_ks2_kernel"),
+    (16, 1, 20_000_000, 4, "map_w_kernel"),
+    (40, 3, 17_000_000, 3, "map_w_kernel"),
 ])
 def test_choice(L_t, H, T, k, kernel, monkeypatch):
     from paper_2608_03893_amd import kvx
