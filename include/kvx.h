@@ -455,13 +455,16 @@ int32_t kvx_version(void);
 
 /* Name of the kernel that kvx_map_cache / kvx_map_cache_slots (n_layers =
  * L_t) or kvx_map_layer (n_layers = 1) would launch for these sizes and
- * element type: with bf16, d == 128, k <= 4, H a multiple of 8 and at least 16
- * target layers, one of the layer-sweep kernels "map_ks2_kernel" (k = 2, 4),
- * "map_ks_kernel" (k = 1, 3) or "map_sweep_kernel" (when neither fits);
- * "map_w_kernel" for the other bf16 cases with d == 128, k <= 4; "map_kernel"
- * for everything else.  The environment variable KVX_KERNEL can override the
- * choice (tuning).  For profiling and benchmarks; a static string, NULL for
- * invalid arguments. */
+ * element type.  With bf16, d == 128 and k <= 4: from 16 target layers on, when
+ * H is a multiple of 8 or the call is long enough to be cut into token segments,
+ * one of the layer-sweep kernels "map_ks2_kernel" (k = 2, 4), "map_ks_kernel"
+ * (k = 1, 3, but for short calls) or "map_sweep_kernel" (when neither can hold
+ * the planes); otherwise "map_w_kernel".  "map_kernel" for everything else.
+ * The first two name both builds of a kernel: a trace shows a call without
+ * KVX_FLAG_WEIGHTS_PACKED as map_ks2_raw_kernel / map_ks_raw_kernel; and
+ * "map_kernel" shows as map_tile_kernel with bf16.  The environment variable
+ * KVX_KERNEL can override the choice (tuning).  For profiling and benchmarks; a
+ * static string, NULL for invalid arguments. */
 const char* kvx_map_kernel_name(const kvx_dims* dims, kvx_dtype dtype, int32_t n_layers);
 
 #ifdef __cplusplus

@@ -48,6 +48,11 @@
 #ifndef KVX_RAW_MAPS
 #define KVX_RAW_MAPS 0
 #endif
+#if KVX_RAW_MAPS
+#define MAP_KS_KERNEL map_ks_raw_kernel
+#else
+#define MAP_KS_KERNEL map_ks_kernel
+#endif
 
 namespace kvx {
 namespace {
@@ -509,7 +514,7 @@ __device__ __forceinline__ void ks_unit(const MapArgs& a, uint32_t lds0, const K
 
 template <int K, int STYLE, bool SLOTS, bool TGT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void map_ks_kernel(const MapArgs a, const SweepPlan p) {
+void MAP_KS_KERNEL(const MapArgs a, const SweepPlan p) {
   __shared__ __attribute__((aligned(256))) char smem[GeoKS<K, SLOTS, TGT>::LDS];
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_u32(smem));
 
@@ -544,7 +549,7 @@ void map_ks_kernel(const MapArgs a, const SweepPlan p) {
 template <int K, int STYLE, bool SLOTS, bool TGT>
 hipError_t launch_ksk(const MapArgs& a, const SweepPlan& p, hipStream_t stream) {
   if constexpr (GeoKS<K, SLOTS, TGT>::fits) {
-    hipLaunchKernelGGL((map_ks_kernel<K, STYLE, SLOTS, TGT>), dim3(256), dim3(NT), 0, stream, a, p);
+    hipLaunchKernelGGL((MAP_KS_KERNEL<K, STYLE, SLOTS, TGT>), dim3(256), dim3(NT), 0, stream, a, p);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;

@@ -63,6 +63,11 @@
 #ifndef KVX_RAW_MAPS
 #define KVX_RAW_MAPS 0
 #endif
+#if KVX_RAW_MAPS
+#define MAP_KS2_KERNEL map_ks2_raw_kernel
+#else
+#define MAP_KS2_KERNEL map_ks2_kernel
+#endif
 
 namespace kvx {
 namespace {
@@ -787,7 +792,7 @@ static_assert(sizeof(MapArgs) + sizeof(Ks2Plan) <= 4096, "kernel arguments");
 
 template <int K, int STYLE, bool SLOTS, bool TGT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void map_ks2_kernel(const MapArgs a, const Ks2Plan kp) {
+void MAP_KS2_KERNEL(const MapArgs a, const Ks2Plan kp) {
   const SweepPlan& p = kp.sp;
   __shared__ __attribute__((aligned(256))) char smem[GeoK2<K, SLOTS, TGT>::LDS];
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_u32(smem));
@@ -824,7 +829,7 @@ void map_ks2_kernel(const MapArgs a, const Ks2Plan kp) {
 template <int K, int STYLE, bool SLOTS, bool TGT>
 hipError_t launch_ks2k(const MapArgs& a, const Ks2Plan& p, hipStream_t stream) {
   if constexpr (GeoK2<K, SLOTS, TGT>::fits) {
-    hipLaunchKernelGGL((map_ks2_kernel<K, STYLE, SLOTS, TGT>), dim3(256), dim3(NT), 0, stream, a, p);
+    hipLaunchKernelGGL((MAP_KS2_KERNEL<K, STYLE, SLOTS, TGT>), dim3(256), dim3(NT), 0, stream, a, p);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;

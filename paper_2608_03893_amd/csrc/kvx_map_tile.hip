@@ -214,7 +214,7 @@ __device__ __forceinline__ void item_add(const MapArgs& a, const TilePlan& p, It
 
 template <int D, int STYLE, bool SLOTS>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void map_kernel(const MapArgs a, const TilePlan p) {
+void map_tile_kernel(const MapArgs a, const TilePlan p) {
   using G = TileGeo<D>;
   constexpr int NB = G::NB, NX = G::NX, NW = G::NW, ND = G::XD + G::WD;
   static_assert(G::LDS <= 160 * 1024, "LDS");
@@ -459,9 +459,9 @@ hipError_t launch_tile(const MapArgs& a, hipStream_t stream) {
   p.per_xcd = (p.items + 7) / 8;
   const dim3 grid((unsigned)(8 * (p.per_xcd < 32 ? p.per_xcd : 32)));
   if (a.slots != nullptr)
-    hipLaunchKernelGGL((map_kernel<D, STYLE, true>), grid, dim3(NTHR), 0, stream, a, p);
+    hipLaunchKernelGGL((map_tile_kernel<D, STYLE, true>), grid, dim3(NTHR), 0, stream, a, p);
   else
-    hipLaunchKernelGGL((map_kernel<D, STYLE, false>), grid, dim3(NTHR), 0, stream, a, p);
+    hipLaunchKernelGGL((map_tile_kernel<D, STYLE, false>), grid, dim3(NTHR), 0, stream, a, p);
   return hipGetLastError();
 }
 
