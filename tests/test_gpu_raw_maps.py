@@ -58,3 +58,56 @@ def test_token_segments(gpu_kvx, H, T, k, L_t):
     tokens = sample_tokens(T, 96, 3, extra=edges)
     got = np32(out[:, :, :, torch.as_tensor(tokens, device=DEV)])
     assert_parity(got, oracle_rows(inp, tokens=tokens), TOL["bf16"], f"H{H} T{T} k{k}")
+
+
+@pytest.mark.parametrize("H,T,k,L_t", [(1, 5157, 4, 32), (3, 5131, 3, 32), (6, 2561, 2, 32), (1, 8200, 1, 40)])
+def test_token_segments_images_slots_second_rope(gpu_kvx, H, T, k, L_t):
+    """Segmented calls with a target RoPE of their own: the images that an unflagged
+    call leaves serve a flagged one, dense and slot-addressed outputs agree with
+    the oracle, and rows that no slot names stay."""
+    cfg = Q.replace(L_s=6, L_t=L_t, H=H, T=T, k=k, rope_src=synth.rope_dict(1e4))
+    kvx = gpu_kvx
+    dims = kvx.Dims(L_s=cfg.L_s, L_t=L_t, H=H, T=T, d=cfg.d, k=k)
+    assert kvx.map_kernel_name(dims) == ("map_ks_kernel" if k in (1, 3) else "map_ks2_kernel")
+    inp = synth.make_inputs(cfg, DEV)
+    ws = torch.full((kvx.workspace_bytes(dims),), 0x7f, dtype=torch.uint8, device=DEV)
+    first = run_gpu(kvx, inp, workspace=ws)
+    tokens = sample_tokens(T, 96, 3, extra=[e for s in range(1, 8) for e in (s * (T // 8), s * (T // 8) + 16)])
+    at = torch.as_tensor(tokens, device=DEV)
+    want = oracle_rows(inp, tokens=tokens)
+    assert_parity(np32(first[:, :, :, at]), want, TOL["bf16"], f"H{H} T{T} k{k} dense")
+
+    slots = torch.arange(T - 1, -1, -1, dtype=torch.int32, device=DEV) + 3
+    slots[5::9] = -1
+    pool = torch.full((L_t, 2, H, T + 8, cfg.d), 7.0, dtype=torch.bfloat16, device=DEV)
+    kvx.map_cache_slots(inp["src"], inp["idx"], inp["W_K"], inp["W_V"], inp["b_K"], inp["b_V"],
+                        inp["rope_src"], inp["rope_tgt"], inp["positions"], slots, pool)
+    kept = at[slots[at] >= 0]
+    assert_parity(np32(pool[:, :, :, slots[kept].long()]), want[:, :, :, np32(slots[at]) >= 0],
+                  TOL["bf16"], f"H{H} T{T} k{k} slots")
+    free = torch.ones(T + 8, dtype=torch.bool, device=DEV)
+    free[slots[slots >= 0].long()] = False
+    assert bool((pool[:, :, :, free] == 7.0).all())
+
+    inp["W_K"], inp["W_V"] = torch.zeros_like(inp["W_K"]), torch.zeros_like(inp["W_V"])
+    again = run_gpu(kvx, inp, workspace=ws, flags=kvx.FLAG_WEIGHTS_PACKED)
+    assert torch.equal(first.view(torch.int16), again.view(torch.int16))
+
+
+@pytest.mark.parametrize("k,L_t,T", [(4, 82, 300), (2, 65, 40), (3, 83, 130), (1, 129, 70)])
+def test_packed_images_of_several_layer_groups(gpu_kvx, k, L_t, T, monkeypatch):
+    # 64 layers and a remainder in one or more groups
+    cfg = Q.replace(L_s=9, L_t=L_t, T=T, k=k)
+    kvx = gpu_kvx
+    if k in (1, 3):
+        monkeypatch.setenv("KVX_KERNEL", "ks")
+    dims = kvx.Dims(L_s=cfg.L_s, L_t=L_t, H=cfg.H, T=T, d=cfg.d, k=k)
+    assert kvx.map_kernel_name(dims) == ("map_ks_kernel" if k in (1, 3) else "map_ks2_kernel")
+    inp = synth.make_inputs(cfg, DEV)
+    ws = torch.full((kvx.workspace_bytes(dims),), 0x7f, dtype=torch.uint8, device=DEV)
+    first = run_gpu(kvx, inp, workspace=ws)
+    layers = [0, 1, 62, 63, 64, L_t - 2, L_t - 1]
+    assert_parity(np32(first[layers]), oracle_rows(inp, layers=layers), TOL["bf16"], f"k{k} L_t{L_t}")
+    inp["W_K"], inp["W_V"] = torch.zeros_like(inp["W_K"]), torch.zeros_like(inp["W_V"])
+    again = run_gpu(kvx, inp, workspace=ws, flags=kvx.FLAG_WEIGHTS_PACKED)
+    assert torch.equal(first.view(torch.int16), again.view(torch.int16))

@@ -189,3 +189,21 @@ def test_xhead_map_layer_and_slots(gpu_kvx):
     untouched = np.setdiff1d(np.arange(S), slots[keep])
     rest = pool.index_select(3, torch.as_tensor(untouched, device=DEV))
     assert bool((rest == -7.0).all()), "a slot outside slot_mapping was written"
+
+
+@pytest.mark.parametrize("d,T", [(128, 8192), (64, 8192), (128, 8191)])
+def test_xhead_strip_planes_in_uneven_parts(gpu_kvx, d, T):
+    """21 key planes over the 8 (d = 128) or 16 (d = 64) parts of the strip pass's
+    grid: several planes a part, a short last part and parts with none, into a
+    workspace that holds NaN before."""
+    cfg = Q.replace(L_s=7, L_t=2, H=3, d=d, k=4, T=T, rope_src=synth.rope_dict(1e4),
+                    rope_tgt=synth.rope_dict(1e4))
+    H_t = 2
+    inp = synth.make_xhead_inputs(cfg, H_t=H_t, device=DEV)
+    dims = gpu_kvx.XDims(L_s=cfg.L_s, L_t=cfg.L_t, H_s=cfg.H, H_t=H_t, T=T, d=d, k=cfg.k)
+    ws = torch.full((gpu_kvx.xhead_workspace_bytes(dims),), 0xff, dtype=torch.uint8, device=DEV)
+    out = _run(gpu_kvx, inp, workspace=ws)
+    assert set(int(v) for v in np.asarray(inp["idx"]).flatten()) >= {6}   # the last plane's layer is read
+    tokens = np.concatenate([np.arange(4), np.arange(31, T, 257), np.arange(T - 4, T)])
+    got = np32(out[:, :, :, torch.as_tensor(tokens, device=DEV)])
+    assert_parity(got, _oracle(inp, tokens=tokens), TOL["bf16"], f"xhead uneven strip d{d} T{T}")
