@@ -90,7 +90,21 @@ struct SweepPlan {
 // (40 layers, one head, 8192 tokens) 134 us against 200; at 10 (20 layers, 6
 // heads, 4096 tokens, k = 3) 227 against 187.
 constexpr int kSegTiles = 20;
-SweepPlan plan_sweep(int nl, int H, int64_t T);
+inline SweepPlan plan_sweep(int nl, int H, int64_t T) {
+  SweepPlan p{};
+  p.full_groups = nl / 64;
+  int r = nl % 64;
+  for (int bit = 32; bit >= 1; bit >>= 1)
+    if (r & bit) p.rest_len[p.n_rest++] = bit;
+  p.n_groups = p.full_groups + p.n_rest;
+  // a head count that does not divide over the eight XCDs: cut the tokens too
+  p.segs = 1;
+  while (H * p.segs % 8 != 0) p.segs *= 2;
+  const int64_t seg_len = T / p.segs;
+  if (p.segs > 1 && seg_len * nl < (int64_t)kSegTiles * 1024 * p.n_groups) p.segs = 1;
+  p.n_units = p.n_groups * H * p.segs * 2;
+  return p;
+}
 
 // Unit u -> (group, K|V, head, token segment) and the CU slot's layer pair and
 // tokens within it.  Within a group, keys cost more vector work than values
@@ -101,8 +115,8 @@ struct SweepUnit {
   bool first;                 // the slot with the pair's first tokens
   int64_t t_begin, t_end;     // empty: nothing for this slot
 };
-__device__ __forceinline__ SweepUnit sweep_unit_of(const SweepPlan& p, int unit, int slot, int H,
-                                                   int32_t T, int tile) {
+__host__ __device__ __forceinline__ SweepUnit sweep_unit_of(const SweepPlan& p, int unit, int slot,
+                                                            int H, int32_t T, int tile) {
   SweepUnit q;
   const int n = H * p.segs;
   const int g = unit / (2 * n);

@@ -494,22 +494,6 @@ hipError_t launch_sstyle(const MapArgs& a, const SweepPlan& p, int style, hipStr
 
 }  // namespace
 
-SweepPlan plan_sweep(int nl, int H, int64_t T) {
-  SweepPlan p{};
-  p.full_groups = nl / 64;
-  int r = nl % 64;
-  for (int bit = 32; bit >= 1; bit >>= 1)
-    if (r & bit) p.rest_len[p.n_rest++] = bit;
-  p.n_groups = p.full_groups + p.n_rest;
-  // a head count that does not divide over the eight XCDs: cut the tokens too
-  p.segs = 1;
-  while (H * p.segs % 8 != 0) p.segs *= 2;
-  const int64_t seg_len = T / p.segs;
-  if (p.segs > 1 && seg_len * nl < (int64_t)kSegTiles * 1024 * p.n_groups) p.segs = 1;
-  p.n_units = p.n_groups * H * p.segs * 2;
-  return p;
-}
-
 hipError_t launch_map_sweep(const MapArgs& a, const SweepPlan& p, int style, hipStream_t stream) {
   if (a.T == 0 || a.nl == 0) return hipSuccess;
   switch (a.k) {
