@@ -121,8 +121,8 @@ size_t tables_bytes(const kvx_dims& m) {
   return (n * 2 * (sizeof(float2) + sizeof(uint32_t)) + 255) / 256 * 256;
 }
 
-// The bf16 kernels for head dimension 128 and k <= 4 read the maps from
-// packed images in the workspace; the general tile kernel reads W as given.
+// The bf16 kernels for head dimension 128 and k <= 4 leave packed images of the
+// maps in the workspace, which calls with KVX_FLAG_WEIGHTS_PACKED read.
 bool packs_weights(const kvx_dims& m, kvx_dtype dt) {
   return dt == KVX_BF16 && m.d == 128 && m.k >= 1 && m.k <= 4;
 }
@@ -298,11 +298,21 @@ Kernel choose_kernel(int dt, const kvx_dims& m, int nl, int64_t tgt_rows, bool s
   if (m.H * segs % 8 == 0 && nl >= 16) {
     // Short calls at k = 1 and 3: a CU's few tiles in the k-split kernel do not
     // cover its unit starts, and the W-stationary kernel's workgroups fill the
-    // chip, but where 64 layers make 32 whole pairs of a few tiles.  Measured, 8
-    // heads, us, k-split / W-stationary: k = 3, 24 layers, 512 tokens 72 / 56;
-    // 80 layers, 1024 tokens 273 / 245; 36 layers, 4096 tokens 409 / 413; 64
-    // layers, 64 tokens 50 / 62; k = 1, 36 layers, 512 tokens 49 / 47, 1024
-    // tokens 83 / 88.
+    // chip, but where 64 layers make 32 whole pairs of a few tiles.  Both costs
+    // grow with the heads (beyond 8, more units and more workgroups), so the line
+    // is one of tokens.  Measured, us, k-split / W-stationary, at 8 and at 16 heads:
+    //   k = 3   20 layers,  512 tokens   63 / 49     128 / 90
+    //           36 layers, 1024 tokens  127 / 134    254 / 256
+    //           64 layers,   64 tokens   47 / 60     119 / 119
+    //           64 layers,  512 tokens  124 / 121    243 / 245
+    //           80 layers, 1024 tokens  256 / 249    505 / 518
+    //   k = 1   36 layers,  256 tokens   34 / 34      59 / 54
+    //           64 layers,  256 tokens   39 / 47      93 / 95
+    //           80 layers,  512 tokens   98 / 90     184 / 177
+    // and with token segments, k = 3, 1024 tokens: 4 heads, 64 layers 111 / 113;
+    // 12 heads, 36 layers 202 / 195.  Layer counts that fall into many groups
+    // would gain beyond this line too, at every k (63 layers, 8 heads, 1024 tokens:
+    // k = 1 150 / 129, k = 4 279 / 243).
     // (16 layers, one group of 8 pairs and 4 token parts, gain least and stay.)
     if (nl > 16 && m.k == 3 && m.T <= 1024 && (nl < 64 || m.T >= 512)) return Kernel::W;
     if (nl > 16 && m.k == 1 && m.T <= 512 && nl < 64) return Kernel::W;

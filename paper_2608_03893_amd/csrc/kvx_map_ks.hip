@@ -189,8 +189,9 @@ __device__ __forceinline__ void ks_unit(const MapArgs& a, uint32_t lds0, const K
         bias[j][i + 1] = hi_bf16(wd);
       }
   }
-  // The map and bias loads are the compiler's own: wait for them here, with a
-  // wait it knows of, so that it inserts none inside the tile loop.
+  // The loads of the bias and of packed maps are the compiler's own: wait for them
+  // here, with a wait it knows of, so that it inserts none inside the tile loop.
+  // (Maps read as given have landed.)
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
   if (KVX_RAW_MAPS) __syncthreads();   // every wave is done with its staging ring: LDS becomes the stage ring
 
