@@ -462,9 +462,10 @@ int32_t kvx_version(void);
  * the planes); otherwise "map_w_kernel".  "map_kernel" for everything else.
  * The first two name both builds of a kernel: a trace shows a call without
  * KVX_FLAG_WEIGHTS_PACKED as map_ks2_raw_kernel / map_ks_raw_kernel; and
- * "map_kernel" shows as map_tile_kernel with bf16.  The environment variable
- * KVX_KERNEL can override the choice (tuning).  For profiling and benchmarks; a
- * static string, NULL for invalid arguments. */
+ * "map_kernel" shows with bf16 as map_tile_kernel or, for short calls at
+ * d == 64, map_short_kernel.  The environment variable KVX_KERNEL can override the
+ * choice (tuning).  For profiling and benchmarks; a static string, NULL for
+ * invalid arguments. */
 const char* kvx_map_kernel_name(const kvx_dims* dims, kvx_dtype dtype, int32_t n_layers);
 
 #ifdef __cplusplus

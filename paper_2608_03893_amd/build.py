@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libkvx.so")
 SOURCES = ["kvx_api.hip", "kvx_kernels.hip", "kvx_map_bf16.hip", "kvx_map_sweep.hip",
-           "kvx_map_ks.hip", "kvx_map_ks_raw.hip", "kvx_map_tile.hip",
+           "kvx_map_ks.hip", "kvx_map_ks_raw.hip", "kvx_map_tile.hip", "kvx_map_short.hip",
            "kvx_map_ks2.hip", "kvx_map_ks2_raw.hip", "kvx_xhead.hip", "kvx_noalloc.hip",
            "kvx_fit.hip", "kvx_mlp.hip"]
 

@@ -60,6 +60,8 @@ hipError_t launch_map(const MapArgs& a, int dtype, int d, int style,
 
 // The bf16 side of launch_map (kvx_map_tile.hip).
 hipError_t launch_map_tile(const MapArgs& a, int d, int style, hipStream_t stream);
+// Its short calls at d = 64 (kvx_map_short.hip).
+hipError_t launch_map_short(const MapArgs& a, int style, hipStream_t stream);
 
 // W-stationary kernel (bf16, d = 128, k <= 4); needs a.cs16, a.cs16_tgt and
 // a.range_len.

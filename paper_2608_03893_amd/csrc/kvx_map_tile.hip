@@ -465,10 +465,42 @@ hipError_t launch_tile(const MapArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Whether a call at d = 64 takes map_short_kernel (64-token workgroups, several on
+// a CU) and not the tile kernel: where the latter's rounds of 256 items, each for
+// 256 tokens however few there are, cost more than the former's workgroups (with
+// interleaved planes 8 of those fit a CU, with half-split ones 6).
+// Measured in whole calls, us, map_tile_kernel / map_short_kernel, with caches
+// warm where the host does not bound the call, else evicted before (e):
+//   k = 1   64 layers, 8 heads     32 tokens  20.6 / 15.4 e    256 tokens  21.9 / 23.9
+//           30 layers, 8 heads   1100 tokens  42.2 / 35.7
+//           32 layers, 8 heads   2500 tokens  93.5 / 84.6     8192 tokens   284 / 294
+//           the same interleaved 2500 tokens  94.0 / 73.4     8192 tokens   287 / 247
+//           one layer, 8 heads   4100 tokens  22.1 / 17.5 e
+//   k = 2   80 layers, 8 heads     64 tokens  21.9 / 17.1      100 tokens  23.1 / 23.4
+//           one layer, 8 heads   4100 tokens  25.9 / 21.1 e
+//   k = 4   80 layers, 8 heads     64 tokens  29.3 / 23.0      100 tokens  30.4 / 36.4
+//           16 layers, 8 heads     64 tokens  18.4 / 21.0 e
+//   k = 8   64 layers, 8 heads     64 tokens  35.9 / 30.8      100 tokens  36.7 / 52.6
+bool short_call(const MapArgs& a, int style) {
+  const int64_t tasks = (int64_t)a.nl * a.H * 2, T = a.T;
+  const int64_t tiles = tasks * ((T + 63) / 64);
+  const int64_t rounds = (tasks * ((T + BT - 1) / BT) + 255) / 256;
+  if (a.k == 1) {
+    const int64_t most = style == 1 ? (tasks <= 640 ? 65536 : 36000) : tasks <= 512 ? 32000 : tasks <= 832 ? 20000 : 0;
+    return tiles <= 700 * rounds || tiles <= most;
+  }
+  if (a.k == 2) {
+    const int64_t most = style == 1 ? 1700 : 1280, per = style == 1 ? 550 : 400;
+    return tiles <= most || tiles <= per * rounds || (tasks <= 32 && tiles <= 4096);
+  }
+  return T <= 64 && tasks > 256;
+}
+
 }  // namespace
 
 hipError_t launch_map_tile(const MapArgs& a, int d, int style, hipStream_t stream) {
   if (a.T == 0 || a.nl == 0) return hipSuccess;
+  if (d == 64 && short_call(a, style)) return launch_map_short(a, style, stream);
   if (d == 128) return style == 0 ? launch_tile<128, 0>(a, stream) : launch_tile<128, 1>(a, stream);
   if (d == 64) return style == 0 ? launch_tile<64, 0>(a, stream) : launch_tile<64, 1>(a, stream);
   return hipErrorInvalidValue;

@@ -52,6 +52,41 @@ def test_tile_parity(gpu_kvx, name):
     assert torch.equal(pool, want), name
 
 
+# Short calls at head dimension 64 have a kernel of their own (64-token tiles, one
+# workgroup each): both sides of its edges, ragged tiles, both RoPE layouts.
+SHORT_CASES = {
+    "k1_T63": Q.replace(d=64, k=1, T=63),
+    "k1_T129_interleaved_rebase": Q.replace(d=64, k=1, H=3, T=129, rope_src=I1,
+                                            rope_tgt=synth.rope_dict(1e4, style=1)),
+    "k1_T1700_rebase": Q.replace(d=64, k=1, H=5, T=1700, rope_src=synth.rope_dict(1e4), bias="none"),
+    "k1_640_tasks_T100": Q.replace(d=64, k=1, L_t=40, H=8, T=100),
+    "k1_640_tasks_T513": Q.replace(d=64, k=1, L_t=40, H=8, T=513),       # the tile kernel again
+    "k2_T300_interleaved": Q.replace(d=64, k=2, T=300, rope_src=I1, rope_tgt=I1),
+    "k3_320_tasks_T64": Q.replace(d=64, k=3, L_t=40, H=4, T=64),
+    "k8_272_tasks_T1": Q.replace(d=64, k=8, L_t=17, H=8, T=1, rope_src=I1, rope_tgt=I1),
+    "k4_320_tasks_T65": Q.replace(d=64, k=4, L_t=40, H=4, T=65),          # the tile kernel again
+}
+
+
+@pytest.mark.parametrize("name", sorted(SHORT_CASES))
+def test_short_parity(gpu_kvx, name):
+    cfg = SHORT_CASES[name]
+    inp = synth.make_inputs(cfg, DEV)
+    out = torch.full((cfg.L_t, 2, cfg.H, cfg.T, cfg.d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    run_gpu(gpu_kvx, inp, out=out)
+    assert_parity(np32(out), oracle_rows(inp), TOL["bf16"], name)
+    slots = torch.arange(cfg.T - 1, -1, -1, dtype=torch.int32, device=DEV) + 5
+    slots[::7] = -1
+    slots[3::7] = cfg.T + 9     # past the pool's end
+    pool = torch.full((cfg.L_t, 2, cfg.H, cfg.T + 9, cfg.d), 7.0, dtype=torch.bfloat16, device=DEV)
+    gpu_kvx.map_cache_slots(inp["src"], inp["idx"], inp["W_K"], inp["W_V"], inp["b_K"], inp["b_V"],
+                            inp["rope_src"], inp["rope_tgt"], inp["positions"], slots, pool)
+    want = torch.full_like(pool, 7.0)
+    keep = ((slots >= 0) & (slots < cfg.T + 9)).nonzero()[:, 0]
+    want[:, :, :, slots[keep].long()] = out[:, :, :, keep]
+    assert torch.equal(pool, want), name
+
+
 F32_CASES = {
     "f32_d128_k3_T65": Q.replace(dtype="f32", k=3, T=65),
     "f32_d128_k1_T1_interleaved": Q.replace(dtype="f32", k=1, T=1, rope_src=I1, rope_tgt=I1, bias="none"),
@@ -70,7 +105,7 @@ def test_f32_tile_parity(gpu_kvx, name):
     assert_parity(np32(run_gpu(gpu_kvx, inp)), oracle_rows(inp), TOL["f32"], name)
 
 
-@pytest.mark.parametrize("d,k", [(64, 2), (128, 5)])
+@pytest.mark.parametrize("d,k", [(64, 2), (64, 4), (128, 5)])
 def test_tile_kernel_leaves_non_finite_rows_alone(gpu_kvx, d, k):
     """A token whose source row holds infinities or NaN spoils its own output row only."""
     cfg = Q.replace(d=d, k=k, T=130)
