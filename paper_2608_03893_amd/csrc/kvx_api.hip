@@ -294,8 +294,14 @@ Kernel choose_kernel(int dt, const kvx_dims& m, int nl, int64_t tgt_rows, bool s
   // spread evenly over the eight XCDs (by heads, or by heads and token
   // segments), and enough layers per group to amortise each unit's start
   // (loading the maps, filling the pipeline).
-  const int segs = kvx::plan_sweep(nl, m.H, m.T).segs;
-  if (m.H * segs % 8 == 0 && nl >= 16) {
+  // Segmented plans read a head's rows once per layer group and segment, so few
+  // groups have to cover the layers.  Measured on 61, 31, 60, 30, 84, 56, 28 and 21
+  // layers, 1 to 6 heads, 6000 to 16384 tokens, W-stationary over k-split: 5 groups
+  // 0.89 - 1.02; 4 groups 0.94 - 1.10; 3 groups k = 1, 3 0.93 - 1.11, k = 2, 4
+  // 0.97 - 1.15; 2 groups 0.98 - 1.17 (but one short call of 80 layers).
+  const kvx::SweepPlan plan = kvx::plan_sweep(nl, m.H, m.T);
+  const bool few_groups = plan.segs == 1 || plan.n_groups <= (m.k % 2 == 0 ? 3 : 2);
+  if (m.H * plan.segs % 8 == 0 && nl >= 16 && few_groups) {
     // Short calls at k = 1 and 3: a CU's few tiles in the k-split kernel do not
     // cover its unit starts, and the W-stationary kernel's workgroups fill the
     // chip, but where 64 layers make 32 whole pairs of a few tiles.  Both costs

@@ -15,6 +15,13 @@ import pytest
     (32, 12, 1280, 2, "map_ks2_kernel"),     # 12 heads: two segments
     (32, 12, 1278, 2, "map_w_kernel"),
     (36, 3, 4096, 3, "map_w_kernel"),
+    # segments over two layer groups, three (k = 2, 4), more
+    (40, 1, 16384, 3, "map_ks_kernel"),
+    (56, 1, 16384, 4, "map_ks2_kernel"),
+    (56, 1, 16384, 3, "map_w_kernel"),
+    (60, 1, 16384, 4, "map_w_kernel"),
+    (63, 1, 65536, 2, "map_w_kernel"),
+    (63, 8, 16384, 2, "map_ks2_kernel"),     # whole heads per XCD
     # short calls at k = 1 and 3
     (36, 8, 1024, 3, "map_w_kernel"),
     (36, 8, 1025, 3, "map_ks_kernel"),
