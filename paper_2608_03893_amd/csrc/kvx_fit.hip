@@ -785,11 +785,11 @@ void gram_kernel(const FitArgs a, const FitPlan p) {
 // A(l % 16, l / 16) and B(l / 16, l % 16), and element i of its result is row
 // 4 i + l / 16, column l % 16.  Copies between global memory and LDS keep 8
 // loads per thread in flight.
-// 64 target layers, 8 heads, k = 4 (1024 tasks, p = 512): 6.4 ms, 10.4 ms with 4
-// waves and register tiles on the vector units.  Of the 6.4 ms the trailing
+// 64 target layers, 8 heads, k = 4 (1024 tasks, p = 512): 6.2 ms, 10.4 ms with 4
+// waves and register tiles on the vector units.  Of the 6.2 ms the trailing
 // updates take about 1.4, the panels' serial chains 1.6, the substitutions 1.5,
-// the diagonal blocks' inverses 0.6.  25 MB a task go beyond L2 (the trailing
-// updates alone 11), 4.0 TB/s over the chip: near the rate of a plain copy.
+// the diagonal blocks' inverses 0.4.  25 MB a task go beyond L2 (the trailing
+// updates alone 11), 4.1 TB/s over the chip: near the rate of a plain copy.
 constexpr int SOLVE_T = 512;   // threads
 constexpr int PLD = 528;       // PT row stride (doubles): >= 512 + 1, 16 mod 32 (half a wave
                                // reads two rows of 16 doubles on distinct banks)
@@ -1097,7 +1097,9 @@ __device__ void solve_sweep(const double* A, double* B, int p, double* sm) {
 // factor's columns read from LDS by all lanes at once.  M_b(r, c), r > c, is
 // stored at A[(r0 + r) p + r0 + c] (the block's unused upper triangle), its
 // diagonal is 1 / L(r, r).  With the column in LDS too, every term waited for
-// its own reads: 0.9 ms of the 7.3 ms solve (1024 tasks, p = 512).
+// its own reads: 0.9 ms of a 7.3 ms solve (1024 tasks, p = 512).  With the lane
+// masks and store addresses kept over the loop, 200 bytes of scratch per lane and
+// 0.2 ms.
 __device__ void invert_diag_blocks(double* A, int p, double* sm) {
   const int wave = threadIdx.x >> 6;
   const int nb = p / SQ;

@@ -15,12 +15,13 @@
 // 64 bytes per instruction, neighbouring lanes in different rows) run at 18
 // bytes per clock and CU even out of L2 (9.7 TB/s over the chip); with 64
 // contiguous bytes per four neighbouring lanes the same loads reach 33 TB/s.
-// Bound at k = 8 by traffic beyond L2 (14.6 GB at 4.2 TB/s: the maps are read
-// again for every 256 tokens), the key strip and the waits around the position
-// barrier (matrix pipe busy about 30%).  Qwen3-14B->32B shapes, k = 8, T = 8191: 3.29 ms (0.67
-// PFLOP/s; 4.35 ms with rows straight into registers and barriers per source
-// layer, 16.95 ms with 64-token tiles staged without a pipeline); head
-// dimension 64, 16 -> 28 layers, k = 4, T = 8192: 0.369 ms (0.415 and 0.667).
+// Bound at k = 8 by traffic beyond L2 (14.7 GB a launch, 4.3 TB/s: the maps are
+// read again for every 256 tokens), the key strip and the waits around the position
+// barrier (matrix pipe busy about 30%).  Qwen3-14B->32B shapes, k = 8, T = 8191:
+// 3.43 ms (0.64 PFLOP/s; 4.35 ms with rows straight into registers and barriers per
+// source layer, 16.95 ms with 64-token tiles staged without a pipeline); one layer
+// of it, 512 tokens 29 us and 2048 tokens 33 us (50 and 75 with 64-token tiles); head
+// dimension 64, 16 -> 28 layers, k = 4, T = 8192: 0.368 ms (0.415 and 0.667).
 //
 // Operand layout: lane L = 16 c + r supplies map row / token r and reduction
 // indices 8 c .. 8 c + 7 of a 32-wide step.  Map row 16 b + 4 c + i holds output
@@ -490,7 +491,7 @@ bool short_call(const MapArgs& a, int style) {
     return tiles <= 700 * rounds || tiles <= most;
   }
   if (a.k == 2) {
-    const int64_t most = style == 1 ? 1700 : 1280, per = style == 1 ? 550 : 400;
+    const int64_t most = style == 1 ? (tasks <= 128 ? 3000 : 1700) : 1280, per = style == 1 ? 550 : 400;
     return tiles <= most || tiles <= per * rounds || (tasks <= 32 && tiles <= 4096);
   }
   return T <= 64 && tasks > 256;

@@ -1,6 +1,7 @@
 """Host-only: the sources that each kernel's traffic figures are tied to are all
 the sources its code comes from."""
 
+import json
 import os
 import re
 import sys
@@ -26,3 +27,14 @@ def includes(name, seen):
 def test_hash_covers_every_include(kernel):
     sources = bench.KERNEL_SOURCES[kernel]
     assert set(sources) == includes(sources[0], set())
+
+
+def test_recorded_counters_are_of_the_current_sources():
+    """bench.py drops a record of other sources in silence: such a record says so.
+    Every record says which run and form it counted."""
+    rec = json.load(open(bench.TRAFFIC_FILE))
+    for workload, kernels in rec.items():
+        for kernel, ent in kernels.items():
+            current = ent["kernel_hash"] == bench.kernel_hash(kernel)
+            assert ent["note"] and (current or "earlier source" in ent["note"]), f"{workload}: {kernel}"
+            assert kernel in ent["kernel"]
